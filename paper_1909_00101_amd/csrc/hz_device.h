@@ -122,122 +122,63 @@ __device__ __forceinline__ void wave_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
-__device__ __forceinline__ double sign1(double b) { return copysign(1.0, b); }
-
-// cos and sin of an angle in (-pi/2, pi/2] from its tangent; an infinite
-// tangent gives cos = 0 and sin = sign of the tangent.
-__device__ __forceinline__ void cs_from_tan(double tn, double &c, double &s)
-{
-    if (isinf(tn)) {
-        c = 0.0;
-        s = sign1(tn);
-    } else {
-        c = 1.0 / sqrt(fma(tn, tn, 1.0));
-        s = tn * c;
-    }
-}
-
-// Real 2x2 implicit Hari-Zimmermann transformation (paper, Section 2.1.2)
-// for the pivot pair A' = [[aii, aij], [aij, ajj]], B' = [[1, x], [x, 1]]:
-// returns Z' = (1/t)[[cos phi, sin phi], [-sin psi, cos psi]] as
-// (z11, z21, z12, z22), z11/z22 being the scaled cosines used by criterion
-// C1.  When A' and B' are proportional (cot 2theta = 0/0) the exceptional
-// congruence of that section is returned, with the sign of x carried onto
-// the off-diagonal entries so that it is a congruence to I for x < 0 too.
-__device__ __forceinline__ void hz_real_2x2(double aii, double ajj, double aij, double x,
-                                            double &z11, double &z21, double &z12, double &z22)
-{
-    const double t = sqrt(fma(-x, x, 1.0));
-    const double h = ajj - aii;
-    const double den = 2.0 * aij - (aii + ajj) * x;
-    if (h == 0.0 && den == 0.0) {
-        const double ax = fabs(x), s = (x < 0.0) ? -1.0 : 1.0;
-        const double r2 = 0.70710678118654752440;
-        const double p = r2 / sqrt(1.0 + ax), q = r2 / sqrt(1.0 - ax);
-        z11 = p;
-        z21 = s * p;
-        z12 = -s * q;
-        z22 = q;
-        return;
-    }
-    const double sp = sqrt(1.0 + x), sm = sqrt(1.0 - x);
-    const double xi = x / (sp + sm);
-    const double eta = x / ((1.0 + sp) * (1.0 + sm));
-    const double cot2 = (t * h) / den;
-    const double tn = sign1(cot2) / (fabs(cot2) + sqrt(fma(cot2, cot2, 1.0)));
-    double c, s;
-    cs_from_tan(tn, c, s);
-    const double cphi = c + xi * (s - eta * c);
-    const double cpsi = c - xi * (s + eta * c);
-    const double sphi = s - xi * (c + eta * s);
-    const double spsi = s + xi * (c - eta * s);
-    z11 = cphi / t;
-    z21 = -spsi / t;
-    z12 = sphi / t;
-    z22 = cpsi / t;
-}
-
-// The real 2x2 transformation of Section 2.1.2 arranged for a short
-// dependency chain on gfx950 (used by the inner solver).  With
-// N = t (a_jj - a_ii) and D = 2 a_ij - (a_ii + a_jj) x, cot 2theta = N / D,
-// and the printed tan theta = sign(cot)/(|cot| + sqrt(1 + cot^2)) equals
-// sign(N) D / q with q = |N| + sqrt(N^2 + D^2) for every (N, D) != (0, 0),
-// including D = 0 (tan = 0) and N = 0 (tan = sign D), so no infinities
-// arise.  Then cos theta = q / sqrt(q^2 + D^2) and sin theta = sign(N) D /
-// sqrt(q^2 + D^2); when D^2 is below the rounding of q^2 the correctly
-// rounded cosine is exactly 1 and is set so (criterion C1 depends on exact
-// ones, as with the printed 1/sqrt(1 + tan^2)).  N^2 is formed as
-// t^2 h^2 so that sqrt(N^2 + D^2) does not wait for t.  The cosines and
-// sines of phi and psi follow as printed, scaled by 1/t.  The exception
-// (N = D = 0, A' proportional to B') returns the signed form of
-// hz_real_2x2.  Returns z11, z21, z12, z22 of Z' (column-major).
+// The real 2x2 implicit Hari-Zimmermann transformation (paper, Section
+// 2.1.2) of the pivot pair A' = [[aii, aij], [aij, ajj]], B' = [[1, x],
+// [x, 1]] in the form in which the inner solver applies it.  Let b be the
+// column with the larger diagonal entry of A' (i when equal) and s the other
+// one; then
+//     b'' = rb b - qb s,   s'' = rr b + rs s
+// diagonalize both forms with B' becoming I, and a''_bb >= a''_ss always: the
+// printed angle 2 theta lies in [-pi/2, pi/2], which keeps the order of the
+// diagonal, so the sorting heuristic needs no transformed diagonal entries.
+// The printed entries are cos phi / t and cos psi / t = rb, rs and the sines
+// rr, -qb in the places that b and s take (t = sqrt(1 - x^2)).
+// With h = a_jj - a_ii and D = 2 a_ij - (a_ii + a_jj) x, tan 2theta =
+// sign(h) D / (t |h|), and the coefficient of b in s'' is the root
+//     r = 2 (min(a_ii, a_jj) x - a_ij) / (|h| + sqrt(t^2 h^2 + D^2)),
+// |r| <= 1, of the quadratic that makes s'' and b'' A'-orthogonal (in the
+// Falk-Langemeyer form of the method; eliminating theta, xi and eta from the
+// printed formulas gives the same number).  B'-orthogonality makes the other
+// one q = (r + x)/(1 + r x), and with w = r + x, o = 1 + r x the squared
+// B'-norms are n_s = w^2 + t^2 and n_b = t^2 n_s / o^2, so that
+//     rs = n_s^(-1/2), rr = r rs, rb = o rs / t, qb = w rs / t:
+// one division and three reciprocal square roots, two of them off the chain,
+// where the printed formulas took two divisions and four.  Every sum of
+// squares is of positive terms and the small column's coefficient r has full
+// relative accuracy: over random pencils of graded diagonals the largest
+// relative A'-offdiagonal left behind is 1.5e-14, against 1.8e-11 for the
+// printed form in doubles; rb, rs are exactly 1 when r and x vanish beside 1
+// (criterion C1).  A' proportional to B' (h = D = 0) takes r = -sign(x), the
+// printed congruence with the sign of x carried onto the off-diagonal
+// entries so that it is one for x < 0 too.  An inner step is bound by the
+// instructions of one wave (about five cycles each), and the transformation
+// with the sort keys was the largest part of them: about 43 instructions
+// instead of 110 took whole solves at the default parameters from 31.8 to
+// 28.0 ms (700 x 256) and from 121.8 to 107.4 ms (2048 x 630), and the tuned
+// 4096 x 1024 solve from 73.2 to 69.1 ms.
 __device__ __forceinline__ void hz_real_2x2_fast(double aii, double ajj, double aij, double x,
-                                                 double &z11, double &z21, double &z12,
-                                                 double &z22, bool &c2small)
+                                                 double &rb, double &qb, double &rs, double &rr,
+                                                 double &t)
 {
     const double t2 = fma(-x, x, 1.0);
     const double h = ajj - aii;
-    const double D = fma(-(aii + ajj), x, 2.0 * aij);
-    if (h == 0.0 && D == 0.0) {
-        const double r2 = 0.70710678118654752440;
-        const double ax = fabs(x), s = (x < 0.0) ? -1.0 : 1.0;
-        const double p = r2 * rsqrt_nr(1.0 + ax), q = r2 * rsqrt_nr(1.0 - ax);
-        z11 = p;
-        z21 = s * p;
-        z12 = -s * q;
-        z22 = q;
-        c2small = false;
-        return;
-    }
-    const double rt = rsqrt_nr(t2);                       // 1/t
-    const double D2 = D * D;
-    const double hyp = sqrt_nr(fma(t2 * h, h, D2));       // sqrt(N^2 + D^2)
-    const double q = fma(t2 * rt, fabs(h), hyp);          // |N| + hyp
-    const double q2 = q * q;
-    const double qd = q2 + D2;
-    const double r = rsqrt_nr(qd);
-    const double sD = (h < 0.0) ? -D : D;                 // sign(N) D
-    const bool tiny = (qd == q2);
-    const double c = tiny ? 1.0 : q * r;
-    const double s = sD * r;
-    // sqrt(1 + x) from one reciprocal square root and sqrt(1 - x) =
-    // t/sqrt(1 + x) with t = t2 * (1/t), both to a few ulps.  xi is divided
-    // out rather than taken as (sqrt(1+x) - sqrt(1-x))/2: for tiny x that
-    // difference cancels, and xi enters the sines of tiny transformations
-    // directly, so it needs relative accuracy.
-    const double rp = rsqrt_nr(1.0 + x);
-    const double sp = (1.0 + x) * rp, sm = (t2 * rt) * rp;
-    const double xi = div_nr(x, sp + sm);
-    const double eta = div_nr(x, (1.0 + sp) * (1.0 + sm));
-    const double cphi = fma(xi, fma(-eta, c, s), c);
-    const double cpsi = fma(-xi, fma(eta, c, s), c);
-    const double sphi = fma(-xi, fma(eta, s, c), s);
-    const double spsi = fma(xi, fma(-eta, s, c), s);
-    z11 = cphi * rt;
-    z21 = -spsi * rt;
-    z12 = sphi * rt;
-    z22 = cpsi * rt;
-    c2small = (cphi == 1.0 && cpsi == 1.0);     // criterion C2 (Section 2.5)
+    const double D = fma(-(aii + ajj), x, aij + aij);
+    const double hyp2 = fma(t2 * h, h, D * D);
+    const double num = fma(fmin(aii, ajj), x, -aij);
+    const double den = fabs(h) + sqrt_nr(hyp2);
+    // num / den to about one ulp; 2 num and not den / 2, which could underflow
+    const double y0 = __builtin_amdgcn_rcp(den);
+    const double e = fma(-den, y0, 1.0);
+    const double r0 = (num + num) * fma(y0, fma(e, e, e), y0);
+    const double r = (hyp2 > 0.0) ? r0 : -copysign(1.0, x);
+    const double w = r + x, o = fma(r, x, 1.0);
+    const double rt = rsqrt_nr(t2);
+    rs = rsqrt_nr(fma(w, w, t2));
+    const double k = rt * rs;
+    rr = r * rs;
+    rb = o * k;
+    qb = w * k;
+    t = t2 * rt;
 }
 
 // The complex 2x2 transformation of Section 2.1.1 without infinities, for

@@ -188,38 +188,37 @@ __device__ __forceinline__ void pair_dots(const double (&fi)[RPL], const double 
 // transformation Z' (real case, Section 2.1.2), its classification (big
 // unless criterion C1, or C2 for variants 4 and 5, says small, Section 2.5)
 // and the sorting heuristic (swap the two columns when the transformed
-// a''_11 < a''_22, or when an orthogonal pair has a_ii < a_jj).  Returns
-// whether [f_i f_j] (and g, z) change: z11, z21, z12, z22 is then the 2x2
-// matrix to postmultiply them by, swap included.
+// a''_11 < a''_22, which is when a_ii < a_jj, or when an orthogonal pair has
+// a_ii < a_jj).  Returns whether [f_i f_j] (and g, z) change: z11, z21, z12,
+// z22 is then the 2x2 matrix to postmultiply them by, swap included; rot and
+// big say whether the pair was transformed and whether by a big
+// transformation.
 __device__ __forceinline__ bool pair_transform(double aii, double ajj, double aij, double bij,
                                                double tol, double tol2, int sort, int variant,
                                                double &z11, double &z21, double &z12,
-                                               double &z22, unsigned &sw_all, unsigned &sw_big)
+                                               double &z22, bool &rot, bool &big)
 {
-    z11 = 1.0; z21 = 0.0; z12 = 0.0; z22 = 1.0;
-    bool swap;
     const bool orth = (aij * aij < aii * ajj * tol2) && (fabs(bij) < tol);
-    if (orth) {
-        swap = sort && (aii < ajj);
+    const bool less = aii < ajj;             // column j is the larger one
+    const bool swap = sort && less;
+    double rb = 1.0, qb = 0.0, rs = 1.0, rr = 0.0, t = 1.0;
+    if (!orth) hz_real_2x2_fast(aii, ajj, aij, bij, rb, qb, rs, rr, t);
+    rot = !orth;
+    // small: criterion C1 (variants 0, 1) or C2 (variants 4, 5), Section 2.5
+    big = rot && ((variant & 4) ? !(rb * t == 1.0 && rs * t == 1.0) : !(rb == 1.0 && rs == 1.0));
+    // sorted, column i gets b'' and column j s''; else each the one it is itself
+    if (sort) {
+        z11 = less ? -qb : rb;
+        z21 = less ? rb : -qb;
+        z12 = less ? rs : rr;
+        z22 = less ? rr : rs;
     } else {
-        bool c2small;
-        hz_real_2x2_fast(aii, ajj, aij, bij, z11, z21, z12, z22, c2small);
-        sw_all += 1;
-        // small: criterion C1 (variants 0, 1) or C2 (variants 4, 5), Section 2.5
-        if ((variant & 4) ? !c2small : !(z11 == 1.0 && z22 == 1.0)) sw_big += 1;
-        swap = false;
-        if (sort) {
-            const double a11 = fma(z11 * z11, aii, fma(2.0 * z11 * z21, aij, z21 * z21 * ajj));
-            const double a22 = fma(z12 * z12, aii, fma(2.0 * z22 * z12, aij, z22 * z22 * ajj));
-            swap = a11 < a22;
-        }
+        z11 = less ? rs : rb;
+        z21 = less ? rr : -qb;
+        z12 = less ? -qb : rr;
+        z22 = less ? rb : rs;
     }
-    if (swap) {
-        double t;
-        t = z11; z11 = z12; z12 = t;
-        t = z21; z21 = z22; z22 = t;
-    }
-    return !orth || swap;
+    return rot || swap;
 }
 
 // [x_i x_j] <- [x_i x_j] [[z11, z12], [z21, z22]] on RPL rows per lane.
@@ -545,8 +544,12 @@ __device__ __forceinline__ void inner_solve(
                         // a negative zero possibly turned positive): with one
                         // path through the step the columns stay in their
                         // registers, where a branch costs a copy of each.
-                        if (pair_transform(aii, ajj, aij, bij, tol, tol2, sort, variant, z11, z21,
-                                           z12, z22, sw_all, sw_big)) {
+                        bool rot, big;
+                        const bool chg = pair_transform(aii, ajj, aij, bij, tol, tol2, sort,
+                                                        variant, z11, z21, z12, z22, rot, big);
+                        sw_all += rot;
+                        sw_big += big;
+                        if (chg) {
                             my_chg = 1;
                             rotate_rows<RPL>(fi, fj, z11, z21, z12, z22);
                             rotate_rows<RPL>(gi, gj, z11, z21, z12, z22);
@@ -576,8 +579,12 @@ __device__ __forceinline__ void inner_solve(
                 load(sZ, cj, zj);
                 double aii, ajj, aij, bij, z11, z21, z12, z22;
                 pair_dots<LP, RPL>(fi, fj, gi, gj, variant, aii, ajj, aij, bij);
-                if (pair_transform(aii, ajj, aij, bij, tol, tol2, sort, variant, z11, z21, z12,
-                                   z22, sw_all, sw_big)) {
+                bool rot, big;
+                const bool chg = pair_transform(aii, ajj, aij, bij, tol, tol2, sort, variant,
+                                                z11, z21, z12, z22, rot, big);
+                sw_all += rot;
+                sw_big += big;
+                if (chg) {
                     my_chg = 1;
                     rotate_rows<RPL>(fi, fj, z11, z21, z12, z22);
                     rotate_rows<RPL>(gi, gj, z11, z21, z12, z22);

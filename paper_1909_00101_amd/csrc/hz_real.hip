@@ -321,14 +321,14 @@ __global__ __launch_bounds__(256) void k_eval_2x2(int64_t count, const double *_
 {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= count) return;
-    double z11, z21, z12, z22;
-    bool c2small;
-    hz_real_2x2_fast(in[4 * i], in[4 * i + 1], in[4 * i + 2], in[4 * i + 3], z11, z21, z12, z22,
-                     c2small);
-    out[4 * i] = z11;
-    out[4 * i + 1] = z21;
-    out[4 * i + 2] = z12;
-    out[4 * i + 3] = z22;
+    const double aii = in[4 * i], ajj = in[4 * i + 1];
+    double rb, qb, rs, rr, t;
+    hz_real_2x2_fast(aii, ajj, in[4 * i + 2], in[4 * i + 3], rb, qb, rs, rr, t);
+    const bool less = aii < ajj;
+    out[4 * i] = less ? rs : rb;
+    out[4 * i + 1] = less ? rr : -qb;
+    out[4 * i + 2] = less ? -qb : rr;
+    out[4 * i + 3] = less ? rb : rs;
 }
 
 // Diagnostic: the device's rounded-down product and its error term
