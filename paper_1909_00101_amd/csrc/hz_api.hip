@@ -576,7 +576,8 @@ int hz_ring_ordering(int N, int lanes, int *table, int *sync)
                             blk * 2 * h + h + ring_col(ssz, nset, u / ssz, u % ssz, p, t);
                     }
                 }
-                if (sync) sync[st] = (t + 1 == ssz) ? 1 : 0;
+                // the workgroup meets where columns pass between waves, and at the end
+                if (sync) sync[st] = (t + 1 == ssz && (h > gw || h == 1)) ? 1 : 0;
             }
     }
     return steps;

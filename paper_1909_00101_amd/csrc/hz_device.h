@@ -59,6 +59,62 @@ __device__ __forceinline__ double dpp_group_sum(double v)
     return v;
 }
 
+// DPP move of a double into lanes of the 4-lane banks in BANKS only (the
+// other lanes keep old): lane n of a 16-lane row reads the lane of the same
+// row that CTRL names.
+template <int CTRL, int BANKS>
+__device__ __forceinline__ double dpp_into(double old, double v)
+{
+    const long long o = __builtin_bit_cast(long long, old), b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp((int)o, (int)b, CTRL, 0xF, BANKS, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(o >> 32), (int)(b >> 32), CTRL, 0xF, BANKS, false);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
+// v_permlane32_swap / v_permlane16_swap on doubles: the upper half of a
+// changes places with the lower half of b (the odd 16-lane rows of a with the
+// even rows of b).
+__device__ __forceinline__ void swap32(double &a, double &b)
+{
+    const long long x = __builtin_bit_cast(long long, a), y = __builtin_bit_cast(long long, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __builtin_bit_cast(double, ((long long)hi[0] << 32) | lo[0]);
+    b = __builtin_bit_cast(double, ((long long)hi[1] << 32) | lo[1]);
+}
+__device__ __forceinline__ void swap16(double &a, double &b)
+{
+    const long long x = __builtin_bit_cast(long long, a), y = __builtin_bit_cast(long long, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __builtin_bit_cast(double, ((long long)hi[0] << 32) | lo[0]);
+    b = __builtin_bit_cast(double, ((long long)hi[1] << 32) | lo[1]);
+}
+
+// Sums of four values over the lanes that share lane mod GW (GW = 4, 8 or 16
+// groups laid side by side in every 16-lane row): the four are reduced
+// together, each swap halving the registers (two rows' partial sums change
+// places and one add does two of them), so that the reduction and the
+// broadcast back take 24 instructions (27 for GW = 4) where a butterfly for
+// each takes 36 (48).  Every lane of a group gets the same bits.
+template <int GW>
+__device__ __forceinline__ void group_sum4(double &s1, double &s2, double &s3, double &s4)
+{
+    swap32(s1, s2);
+    swap32(s3, s4);
+    double u = s1 + s2, v = s3 + s4;         // lower half: s1, s3; upper: s2, s4
+    swap16(u, v);
+    double w = u + v;                        // rows: s1, s3, s2, s4
+    if (GW <= 8) w += dpp_d<0x128>(w);       // row_ror:8
+    if (GW <= 4) w += dpp_d<0x124>(w);       // row_ror:4
+    double x = w;
+    swap16(w, x);                            // w: s1 s1 s2 s2, x: s3 s3 s4 s4
+    s1 = s2 = w;
+    swap32(s1, s2);
+    s3 = s4 = x;
+    swap32(s3, s4);
+}
+
 // Broadcast lane l's double to the wave (two v_readlane_b32; l uniform).
 __device__ __forceinline__ double readlane_d(double v, int l)
 {
@@ -164,7 +220,7 @@ __device__ __forceinline__ void hz_real_2x2_fast(double aii, double ajj, double 
     const double h = ajj - aii;
     const double D = fma(-(aii + ajj), x, aij + aij);
     const double hyp2 = fma(t2 * h, h, D * D);
-    const double num = fma(fmin(aii, ajj), x, -aij);
+    const double num = fma((aii < ajj) ? aii : ajj, x, -aij);
     const double den = fabs(h) + sqrt_nr(hyp2);
     // num / den to about one ulp; 2 num and not den / 2, which could underflow
     const double y0 = __builtin_amdgcn_rcp(den);

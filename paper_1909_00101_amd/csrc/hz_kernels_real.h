@@ -221,17 +221,323 @@ __device__ __forceinline__ bool pair_transform(double aii, double ajj, double ai
     return rot || swap;
 }
 
-// [x_i x_j] <- [x_i x_j] [[z11, z12], [z21, z22]] on RPL rows per lane.
+// [x_i x_j] <- [x_i x_j] [[z11, z12], [z21, z22]] on RPL (even) rows per lane.
+// In assembly so that both columns stay in their registers: written as
+// expressions, x_i came out in fresh ones and was copied back, 24 moves to
+// the 96 products of a step of 2w = 64.  Two rows are interleaved, which covers
+// the latency of the products.
 template <int RPL>
 __device__ __forceinline__ void rotate_rows(double (&xi)[RPL], double (&xj)[RPL], double z11,
                                             double z21, double z12, double z22)
 {
 #pragma unroll
-    for (int r = 0; r < RPL; ++r) {
-        const double ni = fma(xj[r], z21, xi[r] * z11);
-        const double nj = fma(xi[r], z12, xj[r] * z22);
-        xi[r] = ni;
-        xj[r] = nj;
+    for (int r = 0; r < RPL; r += 2) {
+        double t, u;
+        __asm__("v_mul_f64 %[t], %[a], %[z12]\n\t"
+                "v_mul_f64 %[u], %[b], %[z12]\n\t"
+                "v_mul_f64 %[a], %[a], %[z11]\n\t"
+                "v_mul_f64 %[b], %[b], %[z11]\n\t"
+                "v_fma_f64 %[a], %[c], %[z21], %[a]\n\t"
+                "v_fma_f64 %[b], %[d], %[z21], %[b]\n\t"
+                "v_fma_f64 %[c], %[c], %[z22], %[t]\n\t"
+                "v_fma_f64 %[d], %[d], %[z22], %[u]"
+                : [a] "+v"(xi[r]), [b] "+v"(xi[r + 1]), [c] "+v"(xj[r]), [d] "+v"(xj[r + 1]),
+                  [t] "=&v"(t), [u] "=&v"(u)
+                : [z11] "v"(z11), [z21] "v"(z21), [z12] "v"(z12), [z22] "v"(z22));
+    }
+}
+
+// Inner sweeps of the ring ordering (HZ_ORD_RING) with the columns in
+// registers (phases 3 to 5 of the inner solver): F_hat, G_hat come as
+// triangles in sF, sG (column-major, ld W2 + 2); sF, sG, sZ are overwritten.
+//
+// Level by level (blocks of size 2h, h = W, W/2, ..., 1) group u of a block
+// keeps column u of the block's first half for the whole level and meets
+// every column of the second half once.  A wave holds GW = 64 / LP groups,
+// laid side by side in each of its four 16-lane rows (the LP lanes of a group
+// are strided by GW), so that columns pass between the groups of a wave by
+// lane exchanges inside the rows: one DPP move per word from a sub-step to
+// the next, and a masked exchange from a level of h <= GW to the next one.
+// Only the sets of second-half columns of the wider levels, and the change
+// from a wider level to the next, go through LDS, with one barrier each (six
+// for 2w = 64 with 8 lanes).
+//
+// Bound: instructions of one wave per SIMD, about five cycles each.  With the
+// columns handed on through LDS after every sub-step, 12 16-byte stores and
+// 12 loads by each of four waves, the LDS took 1100 of a sub-step's 2290
+// cycles (a store of 64 lanes x 16 bytes costs a compute unit 13 cycles) and
+// nothing overlapped them; the 48 moves take 240.  One inner sweep of 16
+// pivot pairs on which every pair rotates: 64.5 -> 51.8 us at 2w = 64 with 8
+// lanes, 75.7 -> 58.1 with 16, 21.5 -> 15.6 at 2w = 32 with 16 lanes (the 2x2
+// transformation's own gain included).
+template <int W2, int LP>
+__device__ __forceinline__ void ring_solve(double *__restrict__ sF, double *__restrict__ sG,
+                                           double *__restrict__ sZ, unsigned *__restrict__ s_cnt,
+                                           int inner_max, double tol, int sort, int variant,
+                                           double *__restrict__ zt,
+                                           unsigned long long *__restrict__ myc,
+                                           unsigned long long *__restrict__ ph)
+{
+    constexpr int W = W2 / 2, NT = W * LP, RPL = W2 / LP, LDI = W2 + 2;
+    constexpr int GW = 64 / LP;              // groups per wave, and per 16-lane row
+    constexpr int NWV = NT / 64;
+    static_assert(GW == 4 || GW == 8 || GW == 16, "groups fill a 16-lane row");
+    static_assert(W % GW == 0 && RPL % 2 == 0, "whole waves, rows in pairs");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane & (GW - 1), grp = wave * GW + g;
+    const int gl = (lane >> 4) * (16 / GW) + (lane & 15) / GW;   // this lane in its group
+    // rows of a lane's share of a column: pairs 2 LP apart, so that the
+    // 16-byte accesses of a group's lanes are contiguous
+    auto RI = [&](int k) { return (k >> 1) * 2 * LP + 2 * gl + (k & 1); };
+    auto load = [&](const double *M, int c, double (&x)[RPL]) {
+#pragma unroll
+        for (int k = 0; k < RPL; k += 2) {
+            const d2 v = *(const d2 *)(M + c * LDI + RI(k));
+            x[k] = v[0];
+            x[k + 1] = v[1];
+        }
+    };
+    auto store = [&](double *M, int c, const double (&x)[RPL]) {
+#pragma unroll
+        for (int k = 0; k < RPL; k += 2) *(d2 *)(M + c * LDI + RI(k)) = d2{x[k], x[k + 1]};
+    };
+
+    double fi[RPL], gi[RPL], zi[RPL], fj[RPL], gj[RPL], zj[RPL];
+    // 3. first level: group u holds columns u and W + u; prescale by 1/||g_c||
+    load(sF, grp, fi);
+    load(sG, grp, gi);
+    load(sF, W + grp, fj);
+    load(sG, W + grp, gj);
+    {
+        double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) {
+            a = fma(gi[k], gi[k], a);
+            b = fma(gj[k], gj[k], b);
+        }
+        group_sum4<GW>(a, b, c, d);
+        const double di = rsqrt_nr(a), dj = rsqrt_nr(b);
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) {
+            fi[k] *= di;
+            gi[k] *= di;
+            zi[k] = (RI(k) == grp) ? di : 0.0;
+            fj[k] *= dj;
+            gj[k] *= dj;
+            zj[k] = (RI(k) == W + grp) ? dj : 0.0;
+        }
+    }
+    if (ph && tid == 0) ph[3] = wall_clock64();
+
+    // 4. inner sweeps
+    const double tol2 = tol * tol;
+    unsigned n_all = 0, n_big = 0, chg_any = 0;      // wave-uniform, per lane and not per group
+    int nsw = 0;
+    auto step = [&]() {
+        double aii, ajj, aij, bij;
+        if (variant & 1) {
+            double ei, ej, eij, eb;
+            aii = ajj = aij = bij = ei = ej = eij = eb = 0.0;
+#pragma unroll
+            for (int k = 0; k < RPL; ++k) {
+                edot_acc(fi[k], fi[k], aii, ei);
+                edot_acc(fj[k], fj[k], ajj, ej);
+                edot_acc(fi[k], fj[k], aij, eij);
+                edot_acc(gi[k], gj[k], bij, eb);
+            }
+            group_sum4<GW>(aii, ajj, aij, bij);
+            group_sum4<GW>(ei, ej, eij, eb);
+            aii += ei;
+            ajj += ej;
+            aij += eij;
+            bij += eb;
+        } else {
+            aii = ajj = aij = bij = 0.0;
+#pragma unroll
+            for (int k = 0; k < RPL; ++k) {
+                aii = fma(fi[k], fi[k], aii);
+                ajj = fma(fj[k], fj[k], ajj);
+                aij = fma(fi[k], fj[k], aij);
+                bij = fma(gi[k], gj[k], bij);
+            }
+            group_sum4<GW>(aii, ajj, aij, bij);
+        }
+        double z11, z21, z12, z22;
+        bool rot, big;
+        const bool chg = pair_transform(aii, ajj, aij, bij, tol, tol2, sort, variant, z11, z21, z12,
+                                        z22, rot, big);
+        n_all += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(rot));
+        n_big += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(big));
+        // one path for the wave: a pair left alone takes the identity, which
+        // reproduces its columns
+        if (__builtin_amdgcn_ballot_w64(chg)) {
+            chg_any = 1;
+            rotate_rows<RPL>(fi, fj, z11, z21, z12, z22);
+            rotate_rows<RPL>(gi, gj, z11, z21, z12, z22);
+            rotate_rows<RPL>(zi, zj, z11, z21, z12, z22);
+        }
+    };
+    // the second columns of all groups by one lane exchange inside the rows
+#define HZ_MOVE_J(CTRL)                                                                        \
+    _Pragma("unroll") for (int k = 0; k < RPL; ++k)                                            \
+    {                                                                                          \
+        fj[k] = dpp_d<CTRL>(fj[k]);                                                            \
+        gj[k] = dpp_d<CTRL>(gj[k]);                                                            \
+        zj[k] = dpp_d<CTRL>(zj[k]);                                                            \
+    }
+    // exchange of a level h <= GW with the next: groups with bit h/2 set take
+    // their partner's second column as first one, the others their partner's
+    // first one as second
+    auto split = [&](int h, double (&x)[RPL], double (&y)[RPL]) {
+#pragma unroll
+        for (int k = 0; k < RPL; ++k) {
+            const double a = x[k], b = y[k];
+            if (h == 16) {
+                x[k] = dpp_into<0x128, 0xC>(a, b);       // row_ror:8
+                y[k] = dpp_into<0x128, 0x3>(b, a);
+            } else if (h == 8) {
+                x[k] = dpp_into<0x114, 0xA>(a, b);       // row_shr:4
+                y[k] = dpp_into<0x104, 0x5>(b, a);       // row_shl:4
+            } else if (h == 4) {
+                const double p = dpp_d<0x4E>(a), q = dpp_d<0x4E>(b);
+                x[k] = (lane & 2) ? q : a;
+                y[k] = (lane & 2) ? b : p;
+            } else {
+                const double p = dpp_d<0xB1>(a), q = dpp_d<0xB1>(b);
+                x[k] = (lane & 1) ? q : a;
+                y[k] = (lane & 1) ? b : p;
+            }
+        }
+    };
+    for (;;) {
+        const unsigned all0 = n_all;
+        ++nsw;
+        for (int h = W;; h >>= 1) {
+            const int nset = (h > GW) ? h / GW : 1, ssz = (h > GW) ? GW : h;
+            const int at = (grp & -h) * 2;                 // first column of the block
+            for (int p = 0;; ++p) {
+                for (int t = 0;;) {
+                    step();
+                    if (ssz == 1) break;
+                    HZ_MOVE_J(0xB1)                        // xor 1
+                    step();
+                    t += 2;
+                    // on to offset t, or from the last one back to offset 0
+                    const int m = (t < ssz) ? __builtin_ctz(t) : __builtin_ctz(ssz) - 1;
+                    if (m == 0) { HZ_MOVE_J(0xB1) }        // xor 1
+                    else if (m == 1) { HZ_MOVE_J(0x4E) }   // xor 2
+                    else if (m == 2) { HZ_MOVE_J(0x141) }  // xor 7
+                    else { HZ_MOVE_J(0x128) }              // xor 8
+                    if (t >= ssz) break;
+                }
+                if (p + 1 == nset) break;
+                if constexpr (GW < W) {
+                    // the set to its place, the wave's next one from its place
+                    const int ow = wave & (nset - 1);
+                    const int c0 = at + h + GW * ((ow + p) & (nset - 1)) + g;
+                    const int c1 = at + h + GW * ((ow + p + 1) & (nset - 1)) + g;
+                    store(sF, c0, fj);
+                    store(sG, c0, gj);
+                    store(sZ, c0, zj);
+                    __syncthreads();
+                    load(sF, c1, fj);
+                    load(sG, c1, gj);
+                    load(sZ, c1, zj);
+                }
+            }
+            if (h == 1) break;
+            if (h > GW) {
+                if constexpr (GW < W) {
+                    const int ow = wave & (nset - 1), hn = h >> 1;
+                    const int cj = at + h + GW * ((ow + nset - 1) & (nset - 1)) + g;
+                    const int ci = at + (grp & (h - 1));
+                    store(sF, ci, fi);
+                    store(sG, ci, gi);
+                    store(sZ, ci, zi);
+                    store(sF, cj, fj);
+                    store(sG, cj, gj);
+                    store(sZ, cj, zj);
+                    __syncthreads();
+                    const int di = (grp & -hn) * 2 + (grp & (hn - 1)), dj = di + hn;
+                    load(sF, di, fi);
+                    load(sG, di, gi);
+                    load(sZ, di, zi);
+                    load(sF, dj, fj);
+                    load(sG, dj, gj);
+                    load(sZ, dj, zj);
+                }
+            } else {
+#define HZ_SPLIT(H) { split(H, fi, fj); split(H, gi, gj); split(H, zi, zj); }
+                if (h == 2) HZ_SPLIT(2)
+                else if (h == 4) HZ_SPLIT(4)
+                else if (GW >= 8 && h == 8) HZ_SPLIT(8)
+                else if (GW >= 16) HZ_SPLIT(16)
+#undef HZ_SPLIT
+            }
+        }
+        if (nsw >= inner_max) break;
+        // stop after a sweep without transformations; else back to the first level
+        if (lane == 0) s_cnt[wave] = n_all - all0;
+        store(sF, 2 * grp, fi);
+        store(sG, 2 * grp, gi);
+        store(sZ, 2 * grp, zi);
+        store(sF, 2 * grp + 1, fj);
+        store(sG, 2 * grp + 1, gj);
+        store(sZ, 2 * grp + 1, zj);
+        __syncthreads();
+        unsigned any = 0;
+        for (int w = 0; w < NWV; ++w) any |= s_cnt[w];
+        if (__builtin_amdgcn_readfirstlane(any) == 0) break;
+        load(sF, grp, fi);
+        load(sG, grp, gi);
+        load(sZ, grp, zi);
+        load(sF, W + grp, fj);
+        load(sG, W + grp, gj);
+        load(sZ, W + grp, zj);
+    }
+#undef HZ_MOVE_J
+    if (ph && tid == 0) ph[4] = wall_clock64();
+
+    // 5. Theta rescale and write Z_tilde (column-major W2 x W2); the identity
+    // when nothing was transformed or swapped.  The groups hold columns 2 grp
+    // and 2 grp + 1.
+    __syncthreads();                         // s_cnt free
+    if (lane == 0) {
+        s_cnt[3 * wave] = n_all / LP;
+        s_cnt[3 * wave + 1] = n_big / LP;
+        s_cnt[3 * wave + 2] = chg_any;
+    }
+    __syncthreads();
+    unsigned ta = 0, tb = 0, tc = 0;
+    for (int w = 0; w < NWV; ++w) {
+        ta += s_cnt[3 * w];
+        tb += s_cnt[3 * w + 1];
+        tc |= s_cnt[3 * w + 2];
+    }
+    const bool changed = __builtin_amdgcn_readfirstlane(tc) != 0;
+    double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
+#pragma unroll
+    for (int k = 0; k < RPL; ++k) {
+        a = fma(gi[k], gi[k], fma(fi[k], fi[k], a));
+        b = fma(gj[k], gj[k], fma(fj[k], fj[k], b));
+    }
+    group_sum4<GW>(a, b, c, d);
+    const double ti = rsqrt_nr(a), tj = rsqrt_nr(b);
+#pragma unroll
+    for (int k = 0; k < RPL; k += 2) {
+        const int r = RI(k), c0 = 2 * grp;
+        const d2 one = d2{(r == c0) ? 1.0 : 0.0, (r + 1 == c0) ? 1.0 : 0.0};
+        const d2 two = d2{(r == c0 + 1) ? 1.0 : 0.0, (r == c0) ? 1.0 : 0.0};
+        *(d2 *)(zt + c0 * W2 + r) = changed ? d2{zi[k] * ti, zi[k + 1] * ti} : one;
+        *(d2 *)(zt + (c0 + 1) * W2 + r) = changed ? d2{zj[k] * tj, zj[k + 1] * tj} : two;
+    }
+    if (tid == 0) {
+        myc[0] = ta;
+        myc[1] = tb;
+        myc[2] = (unsigned long long)nsw;
+        myc[3] = changed ? 0ull : 1ull;
+        if (ph) ph[5] = wall_clock64();
     }
 }
 
@@ -461,12 +767,13 @@ __device__ __forceinline__ void inner_solve(
         return;
     }
 
+    if constexpr (RING) {
+        ring_solve<W2, LP>(sF, sG, sZ, s_cnt, inner_max, tol, sort, variant, zt, myc, ph);
+        return;
+    }
     const int grp = tid / LP, gl = tid % LP, r0 = gl * RPL;
-    // Row k (0 <= k < RPL) of a lane's share of a column: RPL consecutive
-    // rows for the table orderings; for the ring ordering pairs of rows
-    // 2 LP apart, so that the 16-byte accesses of a group's lanes are
-    // contiguous in LDS.
-    auto RI = [&](int k) { return RING ? (k >> 1) * 2 * LP + 2 * gl + (k & 1) : r0 + k; };
+    // row k (0 <= k < RPL) of a lane's share of a column
+    auto RI = [&](int k) { return r0 + k; };
     // 3. prescale the factor pair: columns 2*grp and 2*grp+1 per group.
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -508,96 +815,35 @@ __device__ __forceinline__ void inner_solve(
     for (int sw = 0; sw < inner_max; ++sw) {
         unsigned sw_all = 0, sw_big = 0;
         ++nsw;
-        if constexpr (RING) {
-            // Ring ordering, level by level: the columns form blocks of size
-            // 2h (h = W, W/2, ..., 1); group u of a block keeps column u of
-            // the block's first half in registers for the whole level and
-            // meets every column of the second half once.  The second half
-            // is cut into sets of G = min(h, groups per wave) columns; in
-            // phase p wave o of the block takes set (o + p) mod (h / G), and
-            // in its sub-step t group g of the wave takes column g xor t of
-            // that set.  A set stays inside one wave for a phase, so the
-            // columns move between sub-steps through LDS in the wave's own
-            // program order; only between phases and levels does the whole
-            // workgroup synchronise.
-            constexpr int GW = 64 / LP;             // groups per wave
-            for (int h = W; h >= 1; h >>= 1) {
-                const int blk = grp / h, u = grp % h;
-                const int ci = blk * 2 * h + u;
-                const int nset = (h >= GW) ? h / GW : 1, ssz = (h >= GW) ? GW : h;
-                const int ow = u / ssz, gw = u % ssz;
-                double fi[RPL], gi[RPL], zi[RPL];
-                load(sF, ci, fi);
-                load(sG, ci, gi);
-                load(sZ, ci, zi);
-                for (int p = 0; p < nset; ++p) {
-                    for (int t = 0; t < ssz; ++t) {
-                        const int cj = blk * 2 * h + h + ring_col(ssz, nset, ow, gw, p, t);
-                        double fj[RPL], gj[RPL], zj[RPL];
-                        load(sF, cj, fj);
-                        load(sG, cj, gj);
-                        load(sZ, cj, zj);
-                        double aii, ajj, aij, bij, z11, z21, z12, z22;
-                        pair_dots<LP, RPL>(fi, fj, gi, gj, variant, aii, ajj, aij, bij);
-                        // Every group applies its 2x2 matrix, the identity when
-                        // its pair is left alone (which reproduces the columns,
-                        // a negative zero possibly turned positive): with one
-                        // path through the step the columns stay in their
-                        // registers, where a branch costs a copy of each.
-                        bool rot, big;
-                        const bool chg = pair_transform(aii, ajj, aij, bij, tol, tol2, sort,
-                                                        variant, z11, z21, z12, z22, rot, big);
-                        sw_all += rot;
-                        sw_big += big;
-                        if (chg) {
-                            my_chg = 1;
-                            rotate_rows<RPL>(fi, fj, z11, z21, z12, z22);
-                            rotate_rows<RPL>(gi, gj, z11, z21, z12, z22);
-                            rotate_rows<RPL>(zi, zj, z11, z21, z12, z22);
-                            store(sF, cj, fj);
-                            store(sG, cj, gj);
-                            store(sZ, cj, zj);
-                        }
-                        if (t + 1 < ssz) wave_fence();
-                    }
-                    __syncthreads();
-                }
+        for (int st = 0; st < isteps; ++st) {
+            const int ci = stab[(st * W + grp) * 2], cj = stab[(st * W + grp) * 2 + 1];
+            double fi[RPL], fj[RPL], gi[RPL], gj[RPL], zi[RPL], zj[RPL];
+            load(sF, ci, fi);
+            load(sF, cj, fj);
+            load(sG, ci, gi);
+            load(sG, cj, gj);
+            load(sZ, ci, zi);
+            load(sZ, cj, zj);
+            double aii, ajj, aij, bij, z11, z21, z12, z22;
+            pair_dots<LP, RPL>(fi, fj, gi, gj, variant, aii, ajj, aij, bij);
+            bool rot, big;
+            const bool chg = pair_transform(aii, ajj, aij, bij, tol, tol2, sort, variant,
+                                            z11, z21, z12, z22, rot, big);
+            sw_all += rot;
+            sw_big += big;
+            if (chg) {
+                my_chg = 1;
+                rotate_rows<RPL>(fi, fj, z11, z21, z12, z22);
+                rotate_rows<RPL>(gi, gj, z11, z21, z12, z22);
+                rotate_rows<RPL>(zi, zj, z11, z21, z12, z22);
                 store(sF, ci, fi);
+                store(sF, cj, fj);
                 store(sG, ci, gi);
+                store(sG, cj, gj);
                 store(sZ, ci, zi);
-                __syncthreads();
+                store(sZ, cj, zj);
             }
-        } else {
-            for (int st = 0; st < isteps; ++st) {
-                const int ci = stab[(st * W + grp) * 2], cj = stab[(st * W + grp) * 2 + 1];
-                double fi[RPL], fj[RPL], gi[RPL], gj[RPL], zi[RPL], zj[RPL];
-                load(sF, ci, fi);
-                load(sF, cj, fj);
-                load(sG, ci, gi);
-                load(sG, cj, gj);
-                load(sZ, ci, zi);
-                load(sZ, cj, zj);
-                double aii, ajj, aij, bij, z11, z21, z12, z22;
-                pair_dots<LP, RPL>(fi, fj, gi, gj, variant, aii, ajj, aij, bij);
-                bool rot, big;
-                const bool chg = pair_transform(aii, ajj, aij, bij, tol, tol2, sort, variant,
-                                                z11, z21, z12, z22, rot, big);
-                sw_all += rot;
-                sw_big += big;
-                if (chg) {
-                    my_chg = 1;
-                    rotate_rows<RPL>(fi, fj, z11, z21, z12, z22);
-                    rotate_rows<RPL>(gi, gj, z11, z21, z12, z22);
-                    rotate_rows<RPL>(zi, zj, z11, z21, z12, z22);
-                    store(sF, ci, fi);
-                    store(sF, cj, fj);
-                    store(sG, ci, gi);
-                    store(sG, cj, gj);
-                    store(sZ, ci, zi);
-                    store(sZ, cj, zj);
-                }
-                __syncthreads();
-            }
+            __syncthreads();
         }
         my_all += sw_all;
         my_big += sw_big;
