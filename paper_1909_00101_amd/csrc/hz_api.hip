@@ -111,6 +111,22 @@ static int inner_table_kind(int inner_ordering)
     return inner_ordering == HZ_ORD_RING ? HZ_ORD_RR : inner_ordering;
 }
 
+// Lanes per column pair in the inner solver.  One inner sweep of 16 pivot
+// pairs on which every pair rotates, 8 against 16 lanes: 2w = 32 22.4 against
+// 18.6 us in round robin and 17.0 against 14.2 in the ring ordering (a step is
+// bound by the instructions that do not shrink with the lanes' shares of the
+// columns, so more waves win); 2w = 64 72.1 against 68.5 in round robin, but 46.4
+// against 53.2 in the ring ordering, which moves columns between lanes and
+// whose second wave per SIMD would only repeat the 2x2 transformations.  2w = 16
+// has 8 column pairs: 8 lanes make one wave.
+static int inner_lanes_for(const hz_params &prm, int W2, int is_complex)
+{
+    if (W2 == 16) return 8;
+    if (prm.inner_lanes) return prm.inner_lanes;
+    if (is_complex) return 8;
+    return (W2 == 64 && prm.inner_ordering == HZ_ORD_RING) ? 8 : 16;
+}
+
 static bool make_plan(const hz_params &prm, int64_t mf, int64_t mg, int64_t n, int is_complex,
                       Plan &P, int mixed = 0)
 {
@@ -142,8 +158,7 @@ static bool make_plan(const hz_params &prm, int64_t mf, int64_t mg, int64_t n, i
     // sequence): 48 gives the real FP64 update of the 4096x1024 pair three
     // workgroups per compute unit
     P.upd_rows = prm.update_rows ? prm.update_rows : 48;
-    P.inner_lp = prm.inner_lanes ? prm.inner_lanes : ((P.W2 == 64) ? 16 : 8);
-    if (P.W2 == 16) P.inner_lp = 8;       // 8 column pairs x 8 lanes: one wave
+    P.inner_lp = inner_lanes_for(prm, P.W2, is_complex);
     const size_t es = P.esz;
     size_t o = 0;
     P.o_fw = o; o = align256(o + es * (size_t)P.mfw * P.nw);
@@ -1290,8 +1305,7 @@ static bool plan_batched(const hz_params &prm, int batch, const int64_t *mf, con
     q.w = L.w;
     L.W2 = 2 * L.w;
     L.isteps = (prm.inner_ordering == HZ_ORD_MM) ? L.W2 : L.W2 - 1;
-    L.inner_lp = prm.inner_lanes ? prm.inner_lanes : (L.W2 == 64 ? 16 : 8);
-    if (L.W2 == 16) L.inner_lp = 8;
+    L.inner_lp = inner_lanes_for(prm, L.W2, 0);
     // The persistent schedule (default where it applies) runs a task's
     // inner solve with the whole workgroup of at least four waves: 2w = 64
     // with 8 or 16 lanes per column pair, 2w = 32 with 16.

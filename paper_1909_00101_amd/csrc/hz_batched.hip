@@ -6,6 +6,8 @@
 // decided on the device after every sweep (paper, Section 2.5 stopping
 // rule per pair); the host replays one captured hipGraph per sweep and
 // reads back a single count of still-active pairs.
+#include <type_traits>
+
 #include "hz_device.h"
 #include "hz_internal.h"
 #include "hz_kernels_real.h"
@@ -61,10 +63,10 @@ __global__ __launch_bounds__(256) void kb_gram(const BProb *__restrict__ probs,
                    P.gram + ((size_t)tk.y * 2 + mat) * (W2 * W2), tile);
 }
 
-template <int W2, int LP, bool RING>
+template <int W2, int LP, int ORD, bool GEN>
 __global__ __launch_bounds__((W2 / 2) * LP) void kb_inner(
     const BProb *__restrict__ probs, const int2 *__restrict__ tasks, const int *__restrict__ active,
-    int step, const int16_t *__restrict__ itab, int isteps, int inner_max, int sort, int variant,
+    int step, int inner_max, int sort, int variant,
     unsigned long long *__restrict__ pcnt, int *__restrict__ pstatus)
 {
     __shared__ unsigned long long c[4];
@@ -73,9 +75,10 @@ __global__ __launch_bounds__((W2 / 2) * LP) void kb_inner(
     const BProb &P = probs[tk.x];
     const double *pa = P.gram + (size_t)tk.y * 2 * (W2 * W2);
     __shared__ __attribute__((aligned(16))) double lds[inner_lds<W2>()];
-    inner_solve<W2, LP, RING>(pa, pa + W2 * W2, 1, 0, itab, isteps, inner_max, P.tol, sort, variant,
-                        P.Zt + (size_t)tk.y * (W2 * W2), c,
-                        pstatus + (size_t)tk.x * ST_NSLOTS, step * 65536 + tk.y, nullptr, lds);
+    inner_solve<W2, LP, ORD, GEN>(pa, pa + W2 * W2, 1, 0, inner_max, P.tol, sort, variant,
+                                  P.Zt + (size_t)tk.y * (W2 * W2), c,
+                                   pstatus + (size_t)tk.x * ST_NSLOTS, step * 65536 + tk.y, nullptr,
+                                   lds);
     __syncthreads();
     if (threadIdx.x == 0) {
         // integer sums: the result does not depend on the order of arrival
@@ -230,13 +233,12 @@ __global__ __launch_bounds__(256) void kb_scatter(const BProb *__restrict__ prob
 // published with a device-scope release before the counter is raised and
 // read after a device-scope acquire.  A wait that exceeds spin_limit polls
 // sets FLAG_STALL on the pair and skips, so the kernel always ends.
-template <int W2, int LP, bool RING>
+template <int W2, int LP, int ORD, bool GEN>
 __global__ __launch_bounds__((W2 / 2) * LP) void kb_persist(
     const BProb *__restrict__ probs, const int2 *__restrict__ tasks, int ntasks,
     int *__restrict__ qhead, unsigned *__restrict__ pdone, int *__restrict__ pfin,
-    unsigned long long *__restrict__ psw, int max_sweeps, const int16_t *__restrict__ itab,
-    int isteps, int inner_max, int sort, int variant, int *__restrict__ pstatus,
-    unsigned spin_limit)
+    unsigned long long *__restrict__ psw, int max_sweeps, int inner_max, int sort,
+    int variant, int *__restrict__ pstatus, unsigned spin_limit)
 {
     constexpr int NT = (W2 / 2) * LP;
     static_assert(NT >= 256 && NT % 64 == 0, "a persistent workgroup has at least four waves");
@@ -330,8 +332,8 @@ __global__ __launch_bounds__((W2 / 2) * LP) void kb_persist(
         gram_block<W2>(P.Gw, P.mgw, pr[0], pr[1], 0, P.mgw / 64, gm + W2 * W2, lds);
         __syncthreads();
         double *const zt = P.Zt + (size_t)l * (W2 * W2);
-        inner_solve<W2, LP, RING>(gm, gm + W2 * W2, 1, 0, itab, isteps, inner_max, P.tol, sort,
-                                  variant, zt, c, st, k * 65536 + l, nullptr, lds);
+        inner_solve<W2, LP, ORD, GEN>(gm, gm + W2 * W2, 1, 0, inner_max, P.tol, sort, variant,
+                                      zt, c, st, k * 65536 + l, nullptr, lds);
         __syncthreads();
         const bool ident = __builtin_amdgcn_readfirstlane(c[3] != 0 ? 1 : 0) != 0;
         if (tid == 0) {
@@ -409,27 +411,32 @@ static void stepb_impl(const BPlan &B, int k, const hz_params &prm, hipStream_t 
     hipLaunchKernelGGL(kb_gram<W2>, dim3(nt, 2), dim3(256), 0, s, B.probs, tasks, B.active, k);
     prof_mark(K_GRAM, false, s);
     prof_mark(K_INNER, true, s);
-    const bool ring = (prm.inner_ordering == HZ_ORD_RING);
     const int lp = (W2 == 16) ? 8 : (B.inner_lp == 4 || B.inner_lp == 16 ? B.inner_lp : 8);
     auto go = [&](auto kern, int l) {
         hipLaunchKernelGGL(kern, dim3(nt), dim3((W2 / 2) * l), 0, s, B.probs, tasks, B.active, k,
-                           B.itab, B.isteps, prm.inner_max_sweeps, prm.sort, prm.variant, B.pcnt,
+                           prm.inner_max_sweeps, prm.sort, prm.variant, B.pcnt,
                            B.pstatus);
     };
-    if (lp == 4) {
-        if constexpr (W2 != 16) {
-            if (ring) go(kb_inner<W2, 4, true>, 4);
-            else go(kb_inner<W2, 4, false>, 4);
+    auto gen = [&](auto gen_c) {
+        constexpr bool GEN = decltype(gen_c)::value;
+        auto lanes = [&](auto lp_c) {
+            constexpr int LP = decltype(lp_c)::value;
+            switch (prm.inner_ordering) {
+            case HZ_ORD_MM: go(kb_inner<W2, LP, HZ_ORD_MM, GEN>, LP); break;
+            case HZ_ORD_RR: go(kb_inner<W2, LP, HZ_ORD_RR, GEN>, LP); break;
+            default: go(kb_inner<W2, LP, HZ_ORD_RING, GEN>, LP); break;
+            }
+        };
+        if constexpr (W2 == 16) {
+            lanes(std::integral_constant<int, 8>());
+        } else {
+            if (lp == 4) lanes(std::integral_constant<int, 4>());
+            else if (lp == 16) lanes(std::integral_constant<int, 16>());
+            else lanes(std::integral_constant<int, 8>());
         }
-    } else if (lp == 16) {
-        if constexpr (W2 != 16) {
-            if (ring) go(kb_inner<W2, 16, true>, 16);
-            else go(kb_inner<W2, 16, false>, 16);
-        }
-    } else {
-        if (ring) go(kb_inner<W2, 8, true>, 8);
-        else go(kb_inner<W2, 8, false>, 8);
-    }
+    };
+    if (prm.variant == 0 && prm.sort) gen(std::false_type());
+    else gen(std::true_type());
     prof_mark(K_INNER, false, s);
     prof_mark(K_UPDATE, true, s);
     hipLaunchKernelGGL(kb_update<W2>, dim3(nt, 3), dim3(256), 0, s, B.probs, tasks, B.active, k);
@@ -449,35 +456,48 @@ void launchb_sweep(const BPlan &B, const hz_params &prm, hipStream_t s)
                        B.pcnt, B.ptot, B.pinfo, B.pstatus, B.nactive);
 }
 
-template <int W2, int LP, bool RING>
-static hipError_t persist_launch(const BPlan &B, const hz_params &prm, hipStream_t s)
+template <int W2, int LP, int ORD, bool GEN>
+static hipError_t persist_launch_gen(const BPlan &B, const hz_params &prm, hipStream_t s)
 {
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kb_persist<W2, LP, RING>,
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kb_persist<W2, LP, ORD, GEN>,
                                                          (W2 / 2) * LP, 0);
     if (e != hipSuccess) return e;
     const int grid = (cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
-    hipLaunchKernelGGL((kb_persist<W2, LP, RING>), dim3(grid), dim3((W2 / 2) * LP), 0, s,
+    hipLaunchKernelGGL((kb_persist<W2, LP, ORD, GEN>), dim3(grid), dim3((W2 / 2) * LP), 0, s,
                        B.probs, B.ptask, B.nptask, B.qhead, B.pdone, B.pfin, B.psw,
-                       prm.max_sweeps, B.itab, B.isteps, prm.inner_max_sweeps, prm.sort,
-                       prm.variant, B.pstatus, 1u << 22);
+                       prm.max_sweeps, prm.inner_max_sweeps, prm.sort, prm.variant,
+                       B.pstatus, 1u << 22);
     return hipGetLastError();
+}
+
+template <int W2, int LP>
+static hipError_t persist_launch(const BPlan &B, const hz_params &prm, hipStream_t s)
+{
+    const bool std = prm.variant == 0 && prm.sort;
+    switch (prm.inner_ordering) {
+    case HZ_ORD_MM:
+        return std ? persist_launch_gen<W2, LP, HZ_ORD_MM, false>(B, prm, s)
+                   : persist_launch_gen<W2, LP, HZ_ORD_MM, true>(B, prm, s);
+    case HZ_ORD_RR:
+        return std ? persist_launch_gen<W2, LP, HZ_ORD_RR, false>(B, prm, s)
+                   : persist_launch_gen<W2, LP, HZ_ORD_RR, true>(B, prm, s);
+    default:
+        return std ? persist_launch_gen<W2, LP, HZ_ORD_RING, false>(B, prm, s)
+                   : persist_launch_gen<W2, LP, HZ_ORD_RING, true>(B, prm, s);
+    }
 }
 
 // The persistent schedule: all sweeps in one launch, then the counter totals.
 hipError_t launchb_persistent(const BPlan &B, const hz_params &prm, hipStream_t s)
 {
-    const bool ring = (prm.inner_ordering == HZ_ORD_RING);
     hipError_t e = hipErrorInvalidValue;
-    if (B.W2 == 64 && B.inner_lp == 16)
-        e = ring ? persist_launch<64, 16, true>(B, prm, s) : persist_launch<64, 16, false>(B, prm, s);
-    else if (B.W2 == 64 && B.inner_lp == 8)
-        e = ring ? persist_launch<64, 8, true>(B, prm, s) : persist_launch<64, 8, false>(B, prm, s);
-    else if (B.W2 == 32 && B.inner_lp == 16)
-        e = ring ? persist_launch<32, 16, true>(B, prm, s) : persist_launch<32, 16, false>(B, prm, s);
+    if (B.W2 == 64 && B.inner_lp == 16) e = persist_launch<64, 16>(B, prm, s);
+    else if (B.W2 == 64 && B.inner_lp == 8) e = persist_launch<64, 8>(B, prm, s);
+    else if (B.W2 == 32 && B.inner_lp == 16) e = persist_launch<32, 16>(B, prm, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kb_persist_totals, dim3((B.batch + 255) / 256), dim3(256), 0, s, B.probs,
                        B.batch, prm.max_sweeps, B.psw, B.pstatus, B.pinfo, B.ptot);

@@ -31,6 +31,8 @@
 // another XCD (and its L2) is seen.  The arithmetic of every task is fixed
 // by (k, l, mat, s, t) alone -- not by which workgroup runs it or when --
 // so the results are bitwise those of the per-step kernels.
+#include <type_traits>
+
 #include "hz_device.h"
 #include "hz_internal.h"
 #include "hz_kernels_real.h"
@@ -129,10 +131,13 @@ __global__ __launch_bounds__(DF_NT) void k_sweep_df(DFArgs A)
             sig = gram_done + kl;
         } else if (kind == DF_INNER) {
             const double *pa = A.part + kl * 2 * S * W2SQ;
-            inner_solve<W2, DF_LP>(pa, pa + S * W2SQ, S, W2SQ, A.itab, A.isteps, A.inner_max,
-                                   A.tol, A.sort, A.variant, A.Zt + kl * W2SQ, A.cnt + kl * 4,
-                                   A.status,
-                                   k * 65536 + l, nullptr, lds);
+            auto solve = [&](auto ord_c) {
+                inner_solve<W2, DF_LP, decltype(ord_c)::value, true>(
+                    pa, pa + S * W2SQ, S, W2SQ, A.inner_max, A.tol, A.sort, A.variant,
+                    A.Zt + kl * W2SQ, A.cnt + kl * 4, A.status, k * 65536 + l, nullptr, lds);
+            };
+            if (A.isteps == W2) solve(std::integral_constant<int, HZ_ORD_MM>());
+            else solve(std::integral_constant<int, HZ_ORD_RR>());
             sig = inner_done + kl;
         } else {
             int64_t tt = sub;

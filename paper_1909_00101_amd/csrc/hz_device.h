@@ -206,15 +206,16 @@ __device__ __forceinline__ void wave_fence()
 // printed form in doubles; rb, rs are exactly 1 when r and x vanish beside 1
 // (criterion C1).  A' proportional to B' (h = D = 0) takes r = -sign(x), the
 // printed congruence with the sign of x carried onto the off-diagonal
-// entries so that it is one for x < 0 too.  An inner step is bound by the
+// entries so that it is one for x < 0 too; with keep (the pair is left alone;
+// the caller passes a_ij = x = 0) it takes r = 0, the identity.  An inner step is bound by the
 // instructions of one wave (about five cycles each), and the transformation
 // with the sort keys was the largest part of them: about 43 instructions
 // instead of 110 took whole solves at the default parameters from 31.8 to
 // 28.0 ms (700 x 256) and from 121.8 to 107.4 ms (2048 x 630), and the tuned
 // 4096 x 1024 solve from 73.2 to 69.1 ms.
 __device__ __forceinline__ void hz_real_2x2_fast(double aii, double ajj, double aij, double x,
-                                                 double &rb, double &qb, double &rs, double &rr,
-                                                 double &t)
+                                                 bool keep, double &rb, double &qb, double &rs,
+                                                 double &rr, double &t)
 {
     const double t2 = fma(-x, x, 1.0);
     const double h = ajj - aii;
@@ -226,7 +227,7 @@ __device__ __forceinline__ void hz_real_2x2_fast(double aii, double ajj, double 
     const double y0 = __builtin_amdgcn_rcp(den);
     const double e = fma(-den, y0, 1.0);
     const double r0 = (num + num) * fma(y0, fma(e, e, e), y0);
-    const double r = (hyp2 > 0.0) ? r0 : -copysign(1.0, x);
+    const double r = (hyp2 > 0.0) ? r0 : (keep ? 0.0 : -copysign(1.0, x));
     const double w = r + x, o = fma(r, x, 1.0);
     const double rt = rsqrt_nr(t2);
     rs = rsqrt_nr(fma(w, w, t2));

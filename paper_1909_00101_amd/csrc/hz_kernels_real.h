@@ -21,10 +21,10 @@ template <int W2> constexpr int update_lds() { return W2 * (W2 + 1); }
 // factorization's own rounding errors (an exactly rank-deficient block, e.g.
 // two equal columns, leaves pivots of either sign of about that size).
 template <int W2> constexpr double PIV_REL() { return W2 * 2.220446049250313e-16; }
-template <int W2> constexpr int inner_lds()
-{
-    return 3 * W2 * (W2 + 2) + 128 + W2 * W2 / 4 + (3 * (W2 / 2) + 1) / 2 + 2;
-}
+// Column stride of the inner solver's tiles in LDS: columns 16 bytes apart
+// modulo the banks.
+template <int W2> constexpr int inner_ld() { return W2 + 2; }
+template <int W2> constexpr int inner_lds() { return 3 * W2 * inner_ld<W2>() + 128 + 16; }
 
 // Device body: four waves form the Gram block of the block-column pair
 // (p, q) of Y (m rows, ld m) over the 64-row chunks [c0, c1) and write it to
@@ -142,83 +142,43 @@ __device__ __forceinline__ void gram_block(const double *__restrict__ Y, int64_t
     }
 }
 
-// The four pivot entries of a column pair held as RPL rows per lane by
-// groups of LP lanes, summed over the group (every lane gets the sums):
-// a_ii = f_i^T f_i, a_jj = f_j^T f_j, a_ij = f_i^T f_j, b_ij = g_i^T g_j
-// (b_ii = b_jj = 1 after the prescaling, Section 2.1).  Odd variants use the
-// enhanced dot products of Appendix A.
-template <int LP, int RPL>
-__device__ __forceinline__ void pair_dots(const double (&fi)[RPL], const double (&fj)[RPL],
-                                          const double (&gi)[RPL], const double (&gj)[RPL],
-                                          int variant, double &aii, double &ajj, double &aij,
-                                          double &bij)
+// The four pivot entries of a column pair (x, y) held as RPL rows per lane,
+// summed over the lanes of its group (group_sum4): a_xx = f_x^T f_x, a_yy,
+// a_xy, b_xy = g_x^T g_y (b_xx = b_yy = 1 after the prescaling, Section 2.1).
+// Odd variants use the enhanced dot products of Appendix A.
+template <int GW, int RPL, bool GEN>
+__device__ __forceinline__ void pair_dots(const double (&fx)[RPL], const double (&fy)[RPL],
+                                          const double (&gx)[RPL], const double (&gy)[RPL],
+                                          int variant, double &axx, double &ayy, double &axy,
+                                          double &bxy)
 {
-    aii = 0.0; ajj = 0.0; aij = 0.0; bij = 0.0;
-    if (variant & 1) {
+    axx = 0.0; ayy = 0.0; axy = 0.0; bxy = 0.0;
+    if (GEN && (variant & 1)) {
         // the rounded-down products and their errors are summed apart
-        double ei = 0.0, ej = 0.0, eij = 0.0, eb = 0.0;
+        double ex = 0.0, ey = 0.0, exy = 0.0, eb = 0.0;
 #pragma unroll
         for (int r = 0; r < RPL; ++r) {
-            edot_acc(fi[r], fi[r], aii, ei);
-            edot_acc(fj[r], fj[r], ajj, ej);
-            edot_acc(fi[r], fj[r], aij, eij);
-            edot_acc(gi[r], gj[r], bij, eb);
+            edot_acc(fx[r], fx[r], axx, ex);
+            edot_acc(fy[r], fy[r], ayy, ey);
+            edot_acc(fx[r], fy[r], axy, exy);
+            edot_acc(gx[r], gy[r], bxy, eb);
         }
-        aii = dpp_group_sum<LP>(aii) + dpp_group_sum<LP>(ei);
-        ajj = dpp_group_sum<LP>(ajj) + dpp_group_sum<LP>(ej);
-        aij = dpp_group_sum<LP>(aij) + dpp_group_sum<LP>(eij);
-        bij = dpp_group_sum<LP>(bij) + dpp_group_sum<LP>(eb);
+        group_sum4<GW>(axx, ayy, axy, bxy);
+        group_sum4<GW>(ex, ey, exy, eb);
+        axx += ex;
+        ayy += ey;
+        axy += exy;
+        bxy += eb;
     } else {
 #pragma unroll
         for (int r = 0; r < RPL; ++r) {
-            aii = fma(fi[r], fi[r], aii);
-            ajj = fma(fj[r], fj[r], ajj);
-            aij = fma(fi[r], fj[r], aij);
-            bij = fma(gi[r], gj[r], bij);
+            axx = fma(fx[r], fx[r], axx);
+            ayy = fma(fy[r], fy[r], ayy);
+            axy = fma(fx[r], fy[r], axy);
+            bxy = fma(gx[r], gy[r], bxy);
         }
-        aii = dpp_group_sum<LP>(aii);
-        ajj = dpp_group_sum<LP>(ajj);
-        aij = dpp_group_sum<LP>(aij);
-        bij = dpp_group_sum<LP>(bij);
+        group_sum4<GW>(axx, ayy, axy, bxy);
     }
-}
-
-// One pointwise step of the inner solver on the pivot entries of column
-// pair (i, j), i < j (Section 2.1): the relative orthogonality test, the 2x2
-// transformation Z' (real case, Section 2.1.2), its classification (big
-// unless criterion C1, or C2 for variants 4 and 5, says small, Section 2.5)
-// and the sorting heuristic (swap the two columns when the transformed
-// a''_11 < a''_22, which is when a_ii < a_jj, or when an orthogonal pair has
-// a_ii < a_jj).  Returns whether [f_i f_j] (and g, z) change: z11, z21, z12,
-// z22 is then the 2x2 matrix to postmultiply them by, swap included; rot and
-// big say whether the pair was transformed and whether by a big
-// transformation.
-__device__ __forceinline__ bool pair_transform(double aii, double ajj, double aij, double bij,
-                                               double tol, double tol2, int sort, int variant,
-                                               double &z11, double &z21, double &z12,
-                                               double &z22, bool &rot, bool &big)
-{
-    const bool orth = (aij * aij < aii * ajj * tol2) && (fabs(bij) < tol);
-    const bool less = aii < ajj;             // column j is the larger one
-    const bool swap = sort && less;
-    double rb = 1.0, qb = 0.0, rs = 1.0, rr = 0.0, t = 1.0;
-    if (!orth) hz_real_2x2_fast(aii, ajj, aij, bij, rb, qb, rs, rr, t);
-    rot = !orth;
-    // small: criterion C1 (variants 0, 1) or C2 (variants 4, 5), Section 2.5
-    big = rot && ((variant & 4) ? !(rb * t == 1.0 && rs * t == 1.0) : !(rb == 1.0 && rs == 1.0));
-    // sorted, column i gets b'' and column j s''; else each the one it is itself
-    if (sort) {
-        z11 = less ? -qb : rb;
-        z21 = less ? rb : -qb;
-        z12 = less ? rs : rr;
-        z22 = less ? rr : rs;
-    } else {
-        z11 = less ? rs : rb;
-        z21 = less ? rr : -qb;
-        z12 = less ? -qb : rr;
-        z22 = less ? rb : rs;
-    }
-    return rot || swap;
 }
 
 // [x_i x_j] <- [x_i x_j] [[z11, z12], [z21, z22]] on RPL (even) rows per lane.
@@ -247,38 +207,54 @@ __device__ __forceinline__ void rotate_rows(double (&xi)[RPL], double (&xj)[RPL]
     }
 }
 
-// Inner sweeps of the ring ordering (HZ_ORD_RING) with the columns in
-// registers (phases 3 to 5 of the inner solver): F_hat, G_hat come as
-// triangles in sF, sG (column-major, ld W2 + 2); sF, sG, sZ are overwritten.
+// Phases 3 to 5 of the inner solver, with the columns in registers: F_hat,
+// G_hat come as triangles in sF, sG (column-major); sF, sG, sZ (ld LDI) are
+// overwritten.  A wave holds GW = 64 / LP lane groups laid side by side in
+// each of its four 16-lane rows (the LP lanes of a group are strided by GW);
+// a group holds a pair of columns, x for as long as the ordering lets it and
+// y for one step.  GEN: any variant, with or without sorting; else variant
+// 0, sorted.
 //
-// Level by level (blocks of size 2h, h = W, W/2, ..., 1) group u of a block
-// keeps column u of the block's first half for the whole level and meets
-// every column of the second half once.  A wave holds GW = 64 / LP groups,
-// laid side by side in each of its four 16-lane rows (the LP lanes of a group
-// are strided by GW), so that columns pass between the groups of a wave by
-// lane exchanges inside the rows: one DPP move per word from a sub-step to
-// the next, and a masked exchange from a level of h <= GW to the next one.
-// Only the sets of second-half columns of the wider levels, and the change
-// from a wider level to the next, go through LDS, with one barrier each (six
-// for 2w = 64 with 8 lanes).
+// RING (HZ_ORD_RING).  Level by level (blocks of size 2h, h = W, W/2, ..., 1)
+// group u of a block keeps column u of the block's first half as x for the
+// whole level and meets every column of the second half once.  The y pass
+// between the groups of a wave by lane exchanges inside the rows: one DPP
+// move per word from a sub-step to the next, and a masked exchange from a
+// level of h <= GW to the next one.  Only the sets of second-half columns of
+// the wider levels, and the change from a wider level to the next, go
+// through LDS, with one barrier each (six for 2w = 64 with 8 lanes).
 //
-// Bound: instructions of one wave per SIMD, about five cycles each.  With the
-// columns handed on through LDS after every sub-step, 12 16-byte stores and
-// 12 loads by each of four waves, the LDS took 1100 of a sub-step's 2290
-// cycles (a store of 64 lanes x 16 bytes costs a compute unit 13 cycles) and
-// nothing overlapped them; the 48 moves take 240.  One inner sweep of 16
-// pivot pairs on which every pair rotates: 64.5 -> 51.8 us at 2w = 64 with 8
-// lanes, 75.7 -> 58.1 with 16, 21.5 -> 15.6 at 2w = 32 with 16 lanes (the 2x2
-// transformation's own gain included).
-template <int W2, int LP>
-__device__ __forceinline__ void ring_solve(double *__restrict__ sF, double *__restrict__ sG,
-                                           double *__restrict__ sZ, unsigned *__restrict__ s_cnt,
-                                           int inner_max, double tol, int sort, int variant,
-                                           double *__restrict__ zt,
-                                           unsigned long long *__restrict__ myc,
-                                           unsigned long long *__restrict__ ph)
+// Round robin and modified modulus.  A step's pairs are those of the tables
+// of hz_ordering; which group takes which pair follows from the step alone,
+// and every column passes on through LDS, with one barrier per step.  For 2w =
+// 64, where the LDS is what bounds a step, a group keeps its x (KEEP): at
+// round-robin step k the kept columns are k, k - 1, ..., k - W + 1 (mod 2W -
+// 1), at modified-modulus step k they are c, c - 1, ..., c - W + 1 (mod 2W) with
+// c = k / 2, so that at most one group changes its x from a step to the next
+// (from the lowest to the one above the highest) while the others pass only
+// their y on; the steps of further sweeps go on from where the last one
+// stopped.  That halves the LDS traffic for eight more selects and one
+// wave's extra stores and loads: 68.5 against 84.4 us for an inner sweep at 2w
+// = 64 with 16 lanes, but 20.4 against 19.9 at 2w = 32.
+//
+// Bound: the instructions of one or two waves per SIMD, about five cycles
+// each from one wave, and in LDS the stores, 13 cycles of a compute unit for
+// 64 lanes x 16 bytes.  With every column handed on through LDS after every
+// step, the pivot sums taken one by one and the orderings read from a table,
+// one inner sweep of 16 pivot pairs on which every pair rotates took, before
+// and now: ring ordering 64.5 -> 46.4 us (2w = 64, 8 lanes) and 21.5 -> 14.2
+// (2w = 32, 16 lanes); round robin 86.9 -> 68.5 (2w = 64, 16 lanes) and 25.5 ->
+// 18.6 (2w = 32, 8 -> 16 lanes).
+template <int W2, int LP, int ORD, bool GEN>
+__device__ __forceinline__ void pointwise_solve(double *__restrict__ sF, double *__restrict__ sG,
+                                                double *__restrict__ sZ,
+                                                unsigned *__restrict__ s_cnt, int inner_max,
+                                                double tol, int sort, int variant,
+                                                double *__restrict__ zt,
+                                                unsigned long long *__restrict__ myc,
+                                                unsigned long long *__restrict__ ph)
 {
-    constexpr int W = W2 / 2, NT = W * LP, RPL = W2 / LP, LDI = W2 + 2;
+    constexpr int W = W2 / 2, NT = W * LP, RPL = W2 / LP, LDI = inner_ld<W2>();
     constexpr int GW = 64 / LP;              // groups per wave, and per 16-lane row
     constexpr int NWV = NT / 64;
     static_assert(GW == 4 || GW == 8 || GW == 16, "groups fill a 16-lane row");
@@ -286,46 +262,72 @@ __device__ __forceinline__ void ring_solve(double *__restrict__ sF, double *__re
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane & (GW - 1), grp = wave * GW + g;
-    const int gl = (lane >> 4) * (16 / GW) + (lane & 15) / GW;   // this lane in its group
-    // rows of a lane's share of a column: pairs 2 LP apart, so that the
-    // 16-byte accesses of a group's lanes are contiguous
-    auto RI = [&](int k) { return (k >> 1) * 2 * LP + 2 * gl + (k & 1); };
-    auto load = [&](const double *M, int c, double (&x)[RPL]) {
+    // Rows of a lane's share of a column: pairs (16 bytes), placed for the
+    // banks.  The columns of neighbouring groups lie 16 bytes apart modulo the
+    // 256 bytes of the banks, and one cycle of a 16-byte load serves lanes 0-3,
+    // 12-15, 20-23 and 24-27 (the next one 4-11, 16-19 and 28-31): sub takes
+    // the places that GW columns leave, and the lowest bit of row, where a
+    // column is long enough, the next 256 bytes -- 5.7 cycles for 64 lanes, 8.3
+    // where the rows meet.
+    const int row = lane >> 4, sub = (lane & 15) / GW;
+    auto RI = [&](int k) {
+        const int kk = k >> 1;
+        const int pair = W2 == 64 ? (GW & 15) * sub + 16 * (row & 1) +
+                                        (GW == 8 ? 4 * (row >> 1) + kk : (row >> 1) + 2 * kk)
+                         : (GW == 8 && W2 == 32) ? row + 8 * sub + 4 * kk
+                                                 : row + 4 * sub + (GW == 16 ? 4 : 0) * kk;
+        return 2 * pair + (k & 1);
+    };
+    auto load = [&](const double *M, int c, double (&v)[RPL]) {
 #pragma unroll
         for (int k = 0; k < RPL; k += 2) {
-            const d2 v = *(const d2 *)(M + c * LDI + RI(k));
-            x[k] = v[0];
-            x[k + 1] = v[1];
+            const d2 p = *(const d2 *)(M + __umul24(c, LDI) + RI(k));
+            v[k] = p[0];
+            v[k + 1] = p[1];
         }
     };
-    auto store = [&](double *M, int c, const double (&x)[RPL]) {
+    auto store = [&](double *M, int c, const double (&v)[RPL]) {
 #pragma unroll
-        for (int k = 0; k < RPL; k += 2) *(d2 *)(M + c * LDI + RI(k)) = d2{x[k], x[k + 1]};
+        for (int k = 0; k < RPL; k += 2) *(d2 *)(M + __umul24(c, LDI) + RI(k)) = d2{v[k], v[k + 1]};
     };
+    double fx[RPL], gx[RPL], zx[RPL], fy[RPL], gy[RPL], zy[RPL];
+    auto load_x = [&](int c) { load(sF, c, fx); load(sG, c, gx); load(sZ, c, zx); };
+    auto load_y = [&](int c) { load(sF, c, fy); load(sG, c, gy); load(sZ, c, zy); };
+    auto store_x = [&](int c) { store(sF, c, fx); store(sG, c, gx); store(sZ, c, zx); };
+    auto store_y = [&](int c) { store(sF, c, fy); store(sG, c, gy); store(sZ, c, zy); };
 
-    double fi[RPL], gi[RPL], zi[RPL], fj[RPL], gj[RPL], zj[RPL];
-    // 3. first level: group u holds columns u and W + u; prescale by 1/||g_c||
-    load(sF, grp, fi);
-    load(sG, grp, gi);
-    load(sF, W + grp, fj);
-    load(sG, W + grp, gj);
+    // the group's first columns
+    constexpr bool RING = ORD == HZ_ORD_RING, MM = ORD == HZ_ORD_MM;
+    constexpr bool KEEP = !RING && W2 == 64;
+    int cx = grp, cy = W + grp;
+    if (!RING) cy = MM ? (grp ? W2 - grp : W) : W2 - 1 - grp;
+    if (KEEP) {
+        cx = MM ? ((W2 - grp) & (W2 - 1)) : (grp ? W2 - 1 - grp : 0);
+        cy = MM ? (grp ? grp : W) : (grp ? grp : W2 - 1);
+    }
+
+    // 3. prescale by 1/||g_c||
+    load(sF, cx, fx);
+    load(sG, cx, gx);
+    load(sF, cy, fy);
+    load(sG, cy, gy);
     {
         double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
 #pragma unroll
         for (int k = 0; k < RPL; ++k) {
-            a = fma(gi[k], gi[k], a);
-            b = fma(gj[k], gj[k], b);
+            a = fma(gx[k], gx[k], a);
+            b = fma(gy[k], gy[k], b);
         }
         group_sum4<GW>(a, b, c, d);
-        const double di = rsqrt_nr(a), dj = rsqrt_nr(b);
+        const double dx = rsqrt_nr(a), dy = rsqrt_nr(b);
 #pragma unroll
         for (int k = 0; k < RPL; ++k) {
-            fi[k] *= di;
-            gi[k] *= di;
-            zi[k] = (RI(k) == grp) ? di : 0.0;
-            fj[k] *= dj;
-            gj[k] *= dj;
-            zj[k] = (RI(k) == W + grp) ? dj : 0.0;
+            fx[k] *= dx;
+            gx[k] *= dx;
+            zx[k] = (RI(k) == cx) ? dx : 0.0;
+            fy[k] *= dy;
+            gy[k] *= dy;
+            zy[k] = (RI(k) == cy) ? dy : 0.0;
         }
     }
     if (ph && tid == 0) ph[3] = wall_clock64();
@@ -334,174 +336,249 @@ __device__ __forceinline__ void ring_solve(double *__restrict__ sF, double *__re
     const double tol2 = tol * tol;
     unsigned n_all = 0, n_big = 0, chg_any = 0;      // wave-uniform, per lane and not per group
     int nsw = 0;
-    auto step = [&]() {
-        double aii, ajj, aij, bij;
-        if (variant & 1) {
-            double ei, ej, eij, eb;
-            aii = ajj = aij = bij = ei = ej = eij = eb = 0.0;
-#pragma unroll
-            for (int k = 0; k < RPL; ++k) {
-                edot_acc(fi[k], fi[k], aii, ei);
-                edot_acc(fj[k], fj[k], ajj, ej);
-                edot_acc(fi[k], fj[k], aij, eij);
-                edot_acc(gi[k], gj[k], bij, eb);
-            }
-            group_sum4<GW>(aii, ajj, aij, bij);
-            group_sum4<GW>(ei, ej, eij, eb);
-            aii += ei;
-            ajj += ej;
-            aij += eij;
-            bij += eb;
-        } else {
-            aii = ajj = aij = bij = 0.0;
-#pragma unroll
-            for (int k = 0; k < RPL; ++k) {
-                aii = fma(fi[k], fi[k], aii);
-                ajj = fma(fj[k], fj[k], ajj);
-                aij = fma(fi[k], fj[k], aij);
-                bij = fma(gi[k], gj[k], bij);
-            }
-            group_sum4<GW>(aii, ajj, aij, bij);
+
+    // One pointwise step on the group's pair (Section 2.1): the relative
+    // orthogonality test, the 2x2 transformation, its classification (big
+    // unless criterion C1, or C2 for variants 4 and 5, says small, Section
+    // 2.5) and the sorting heuristic: the column with the smaller index gets
+    // the larger transformed diagonal entry, which is b'' (or the larger
+    // column of a pair that is orthogonal already).  first: x has the smaller
+    // index (always, unless KEEP).  A pair that is left alone takes the
+    // identity -- its x and a count as zero, which gives it exactly -- so that
+    // the wave has one path; a wave in which every pair is left alone skips
+    // it.  The lane masks are taken from plain comparisons, which cost one
+    // instruction each.
+    auto step = [&](bool first) {
+        double axx, ayy, axy, bxy;
+        pair_dots<GW, RPL, GEN>(fx, fy, gx, gy, variant, axx, ayy, axy, bxy);
+        const bool orth_a = axy * axy < axx * ayy * tol2, orth_b = fabs(bxy) < tol;
+        const bool lt = axx < ayy, gt = ayy < axx;
+        const unsigned long long m_rot = ~(__builtin_amdgcn_ballot_w64(orth_a) &
+                                           __builtin_amdgcn_ballot_w64(orth_b));
+        // x is s, the smaller one (of equal ones, the one with the larger index),
+        // and x gets b''; they change places where both or neither holds
+        const bool xs = KEEP ? (first ? lt : !gt) : lt;
+        const bool xb = (GEN && !sort) ? !xs : (KEEP ? first : true);
+        const unsigned long long m_lt = __builtin_amdgcn_ballot_w64(lt),
+                                 m_gt = __builtin_amdgcn_ballot_w64(gt);
+        unsigned long long m_swap = m_lt;
+        if (KEEP) {
+            const unsigned long long m_first = __builtin_amdgcn_ballot_w64(first);
+            m_swap = (m_first & m_lt) | (~m_first & m_gt);
         }
-        double z11, z21, z12, z22;
-        bool rot, big;
-        const bool chg = pair_transform(aii, ajj, aij, bij, tol, tol2, sort, variant, z11, z21, z12,
-                                        z22, rot, big);
-        n_all += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(rot));
-        n_big += (unsigned)__popcll(__builtin_amdgcn_ballot_w64(big));
-        // one path for the wave: a pair left alone takes the identity, which
-        // reproduces its columns
-        if (__builtin_amdgcn_ballot_w64(chg)) {
-            chg_any = 1;
-            rotate_rows<RPL>(fi, fj, z11, z21, z12, z22);
-            rotate_rows<RPL>(gi, gj, z11, z21, z12, z22);
-            rotate_rows<RPL>(zi, zj, z11, z21, z12, z22);
+        if (GEN && !sort) m_swap = 0;
+        if ((m_rot | m_swap) == 0) return;
+        chg_any = 1;
+        const bool orth = orth_a && orth_b;
+        double rb, qb, rs, rr, t;
+        hz_real_2x2_fast(axx, ayy, orth ? 0.0 : axy, orth ? 0.0 : bxy, orth, rb, qb, rs, rr, t);
+        unsigned long long m_big;
+        if (GEN && (variant & 4))                              // criterion C2
+            m_big = __builtin_amdgcn_ballot_w64(rb * t != 1.0) |
+                    __builtin_amdgcn_ballot_w64(rs * t != 1.0);
+        else                                                   // criterion C1
+            m_big = __builtin_amdgcn_ballot_w64(rb != 1.0) | __builtin_amdgcn_ballot_w64(rs != 1.0);
+        n_all += (unsigned)__popcll(m_rot);
+        n_big += (unsigned)__popcll(m_rot & m_big);
+        // coefficients of x and y in b'' and s''
+        const double bx = xs ? -qb : rb, by = xs ? rb : -qb;
+        const double sx = xs ? rs : rr, sy = xs ? rr : rs;
+        double z11 = bx, z21 = by, z12 = sx, z22 = sy;
+        if (KEEP || GEN) {
+            z11 = xb ? bx : sx;
+            z21 = xb ? by : sy;
+            z12 = xb ? sx : bx;
+            z22 = xb ? sy : by;
         }
+        rotate_rows<RPL>(fx, fy, z11, z21, z12, z22);
+        rotate_rows<RPL>(gx, gy, z11, z21, z12, z22);
+        rotate_rows<RPL>(zx, zy, z11, z21, z12, z22);
     };
-    // the second columns of all groups by one lane exchange inside the rows
-#define HZ_MOVE_J(CTRL)                                                                        \
+
+    if constexpr (RING) {
+        // the y of all groups by one lane exchange inside the rows
+#define HZ_MOVE_Y(CTRL)                                                                        \
     _Pragma("unroll") for (int k = 0; k < RPL; ++k)                                            \
     {                                                                                          \
-        fj[k] = dpp_d<CTRL>(fj[k]);                                                            \
-        gj[k] = dpp_d<CTRL>(gj[k]);                                                            \
-        zj[k] = dpp_d<CTRL>(zj[k]);                                                            \
+        fy[k] = dpp_d<CTRL>(fy[k]);                                                            \
+        gy[k] = dpp_d<CTRL>(gy[k]);                                                            \
+        zy[k] = dpp_d<CTRL>(zy[k]);                                                            \
     }
-    // exchange of a level h <= GW with the next: groups with bit h/2 set take
-    // their partner's second column as first one, the others their partner's
-    // first one as second
-    auto split = [&](int h, double (&x)[RPL], double (&y)[RPL]) {
+        // exchange of a level h <= GW with the next: groups with bit h/2 set
+        // take their partner's y as x, the others their partner's x as y
+        auto split = [&](int h, double (&x)[RPL], double (&y)[RPL]) {
 #pragma unroll
-        for (int k = 0; k < RPL; ++k) {
-            const double a = x[k], b = y[k];
-            if (h == 16) {
-                x[k] = dpp_into<0x128, 0xC>(a, b);       // row_ror:8
-                y[k] = dpp_into<0x128, 0x3>(b, a);
-            } else if (h == 8) {
-                x[k] = dpp_into<0x114, 0xA>(a, b);       // row_shr:4
-                y[k] = dpp_into<0x104, 0x5>(b, a);       // row_shl:4
-            } else if (h == 4) {
-                const double p = dpp_d<0x4E>(a), q = dpp_d<0x4E>(b);
-                x[k] = (lane & 2) ? q : a;
-                y[k] = (lane & 2) ? b : p;
-            } else {
-                const double p = dpp_d<0xB1>(a), q = dpp_d<0xB1>(b);
-                x[k] = (lane & 1) ? q : a;
-                y[k] = (lane & 1) ? b : p;
-            }
-        }
-    };
-    for (;;) {
-        const unsigned all0 = n_all;
-        ++nsw;
-        for (int h = W;; h >>= 1) {
-            const int nset = (h > GW) ? h / GW : 1, ssz = (h > GW) ? GW : h;
-            const int at = (grp & -h) * 2;                 // first column of the block
-            for (int p = 0;; ++p) {
-                for (int t = 0;;) {
-                    step();
-                    if (ssz == 1) break;
-                    HZ_MOVE_J(0xB1)                        // xor 1
-                    step();
-                    t += 2;
-                    // on to offset t, or from the last one back to offset 0
-                    const int m = (t < ssz) ? __builtin_ctz(t) : __builtin_ctz(ssz) - 1;
-                    if (m == 0) { HZ_MOVE_J(0xB1) }        // xor 1
-                    else if (m == 1) { HZ_MOVE_J(0x4E) }   // xor 2
-                    else if (m == 2) { HZ_MOVE_J(0x141) }  // xor 7
-                    else { HZ_MOVE_J(0x128) }              // xor 8
-                    if (t >= ssz) break;
-                }
-                if (p + 1 == nset) break;
-                if constexpr (GW < W) {
-                    // the set to its place, the wave's next one from its place
-                    const int ow = wave & (nset - 1);
-                    const int c0 = at + h + GW * ((ow + p) & (nset - 1)) + g;
-                    const int c1 = at + h + GW * ((ow + p + 1) & (nset - 1)) + g;
-                    store(sF, c0, fj);
-                    store(sG, c0, gj);
-                    store(sZ, c0, zj);
-                    __syncthreads();
-                    load(sF, c1, fj);
-                    load(sG, c1, gj);
-                    load(sZ, c1, zj);
+            for (int k = 0; k < RPL; ++k) {
+                const double a = x[k], b = y[k];
+                if (h == 16) {
+                    x[k] = dpp_into<0x128, 0xC>(a, b);       // row_ror:8
+                    y[k] = dpp_into<0x128, 0x3>(b, a);
+                } else if (h == 8) {
+                    x[k] = dpp_into<0x114, 0xA>(a, b);       // row_shr:4
+                    y[k] = dpp_into<0x104, 0x5>(b, a);       // row_shl:4
+                } else if (h == 4) {
+                    const double p = dpp_d<0x4E>(a), q = dpp_d<0x4E>(b);
+                    x[k] = (lane & 2) ? q : a;
+                    y[k] = (lane & 2) ? b : p;
+                } else {
+                    const double p = dpp_d<0xB1>(a), q = dpp_d<0xB1>(b);
+                    x[k] = (lane & 1) ? q : a;
+                    y[k] = (lane & 1) ? b : p;
                 }
             }
-            if (h == 1) break;
-            if (h > GW) {
-                if constexpr (GW < W) {
-                    const int ow = wave & (nset - 1), hn = h >> 1;
-                    const int cj = at + h + GW * ((ow + nset - 1) & (nset - 1)) + g;
-                    const int ci = at + (grp & (h - 1));
-                    store(sF, ci, fi);
-                    store(sG, ci, gi);
-                    store(sZ, ci, zi);
-                    store(sF, cj, fj);
-                    store(sG, cj, gj);
-                    store(sZ, cj, zj);
-                    __syncthreads();
-                    const int di = (grp & -hn) * 2 + (grp & (hn - 1)), dj = di + hn;
-                    load(sF, di, fi);
-                    load(sG, di, gi);
-                    load(sZ, di, zi);
-                    load(sF, dj, fj);
-                    load(sG, dj, gj);
-                    load(sZ, dj, zj);
+        };
+        for (;;) {
+            const unsigned all0 = n_all;
+            ++nsw;
+            for (int h = W;; h >>= 1) {
+                const int nset = (h > GW) ? h / GW : 1, ssz = (h > GW) ? GW : h;
+                const int at = (grp & -h) * 2;                 // first column of the block
+                const int ow = wave & (nset - 1);
+                for (int p = 0;; ++p) {
+                    // the offsets ring_off(0 .. ssz - 1) and back to 0, four at a time
+                    for (int t = 0;;) {
+                        step(true);
+                        if (ssz == 1) break;
+                        HZ_MOVE_Y(0xB1)                        // xor 1
+                        step(true);
+                        if (ssz == 2) {
+                            HZ_MOVE_Y(0xB1)
+                            break;
+                        }
+                        HZ_MOVE_Y(0x4E)                        // xor 2
+                        step(true);
+                        HZ_MOVE_Y(0xB1)
+                        step(true);
+                        t += 4;
+                        if (ssz == 4) {
+                            HZ_MOVE_Y(0x4E)
+                        } else if (GW == 16 && ssz == 16 && (t & 7) == 0) {
+                            HZ_MOVE_Y(0x128)                   // xor 8
+                        } else {
+                            HZ_MOVE_Y(0x141)                   // xor 7
+                        }
+                        if (t >= ssz) break;
+                    }
+                    if (p + 1 == nset) break;
+                    if constexpr (GW < W) {
+                        // the set to its place, the wave's next one from its place
+                        store_y(at + h + GW * ((ow + p) & (nset - 1)) + g);
+                        __syncthreads();
+                        load_y(at + h + GW * ((ow + p + 1) & (nset - 1)) + g);
+                    }
                 }
-            } else {
-#define HZ_SPLIT(H) { split(H, fi, fj); split(H, gi, gj); split(H, zi, zj); }
-                if (h == 2) HZ_SPLIT(2)
-                else if (h == 4) HZ_SPLIT(4)
-                else if (GW >= 8 && h == 8) HZ_SPLIT(8)
-                else if (GW >= 16) HZ_SPLIT(16)
+                if (h == 1) break;
+                if (h > GW) {
+                    if constexpr (GW < W) {
+                        const int hn = h >> 1, c = (grp & -hn) * 2 + (grp & (hn - 1));
+                        store_x(at + (grp & (h - 1)));
+                        store_y(at + h + GW * ((ow + nset - 1) & (nset - 1)) + g);
+                        __syncthreads();
+                        load_x(c);
+                        load_y(c + hn);
+                    }
+                } else {
+#define HZ_SPLIT(H) { split(H, fx, fy); split(H, gx, gy); split(H, zx, zy); }
+                    if (h == 2) HZ_SPLIT(2)
+                    else if (h == 4) HZ_SPLIT(4)
+                    else if (GW >= 8 && h == 8) HZ_SPLIT(8)
+                    else if (GW >= 16) HZ_SPLIT(16)
 #undef HZ_SPLIT
+                }
             }
+            if (nsw >= inner_max) break;
+            // stop after a sweep without transformations; else back to the first level
+            if (lane == 0) s_cnt[wave] = n_all - all0;
+            store_x(2 * grp);
+            store_y(2 * grp + 1);
+            __syncthreads();
+            unsigned any = 0;
+            for (int w = 0; w < NWV; ++w) any |= s_cnt[w];
+            if (__builtin_amdgcn_readfirstlane(any) == 0) break;
+            load_x(grp);
+            load_y(W + grp);
         }
-        if (nsw >= inner_max) break;
-        // stop after a sweep without transformations; else back to the first level
-        if (lane == 0) s_cnt[wave] = n_all - all0;
-        store(sF, 2 * grp, fi);
-        store(sG, 2 * grp, gi);
-        store(sZ, 2 * grp, zi);
-        store(sF, 2 * grp + 1, fj);
-        store(sG, 2 * grp + 1, gj);
-        store(sZ, 2 * grp + 1, zj);
-        __syncthreads();
-        unsigned any = 0;
-        for (int w = 0; w < NWV; ++w) any |= s_cnt[w];
-        if (__builtin_amdgcn_readfirstlane(any) == 0) break;
-        load(sF, grp, fi);
-        load(sG, grp, gi);
-        load(sZ, grp, zi);
-        load(sF, W + grp, fj);
-        load(sG, W + grp, gj);
-        load(sZ, W + grp, zj);
+        cx = 2 * grp;
+        cy = 2 * grp + 1;
+#undef HZ_MOVE_Y
+    } else {
+        constexpr int M = W2 - 1, ISTEPS = MM ? W2 : M;
+        int kp = 0, kc = 0;      // step mod 2W - 1 (round robin) or 4W (modified modulus); c
+        unsigned p = cx, q = cy; // !KEEP, round robin: the pair before it is ordered
+        // both move on by one mod 2W - 1, but for the q = 2W - 1 of grp 0
+        const unsigned qinc = grp ? 1 : 0, qmod = grp ? M : 1u << 31;
+        int nx, ny;
+        bool out = true, in = true;
+        auto plan = [&]() {
+            if constexpr (!KEEP && !MM) {
+                p = min(p + 1, p + 1 - M);       // unsigned: the second wraps while p + 1 < M
+                q = min(q + qinc, q + qinc - qmod);
+                nx = min(p, q);
+                ny = max(p, q);
+                return;
+            }
+            const bool adv = !MM || (kp & 1);
+            kp = MM ? (kp + 1) & (2 * W2 - 1) : (kp + 1 < M ? kp + 1 : 0);
+            int pos = grp;
+            if (KEEP) {
+                const bool mine = adv && ((W - 1 - kc) & (W - 1)) / GW == wave;
+                out = mine && ((kc + grp) & (W - 1)) == W - 1;
+                if (adv) ++kc;
+                pos = (kc + grp) & (W - 1);
+                in = mine && pos == 0;
+            }
+            int x, y;
+            if (MM) {
+                x = ((kp >> 1) - pos) & (W2 - 1);
+                y = (kp - x) & (W2 - 1);
+                y = (y == x) ? x ^ W : y;
+            } else {
+                x = kp - pos;
+                x += (x < 0) ? M : 0;
+                y = kp + pos;
+                y -= (y >= M) ? M : 0;
+                y = (pos == 0) ? M : y;
+            }
+            nx = KEEP ? x : min(x, y);
+            ny = KEEP ? y : max(x, y);
+        };
+        auto leave = [&]() {
+            store_y(cy);
+            if (!KEEP || out) store_x(cx);
+        };
+        auto enter = [&]() {
+            cx = nx;
+            cy = ny;
+            load_y(cy);
+            if (!KEEP || in) load_x(cx);
+        };
+        for (;;) {
+            const unsigned all0 = n_all;
+            ++nsw;
+            for (int st = 1; st < ISTEPS; ++st) {
+                plan();
+                step(cx < cy);
+                leave();
+                __syncthreads();
+                enter();
+            }
+            step(cx < cy);
+            if (nsw >= inner_max) break;
+            // stop after a sweep without transformations
+            plan();
+            leave();
+            if (lane == 0) s_cnt[wave] = n_all - all0;
+            __syncthreads();
+            unsigned any = 0;
+            for (int w = 0; w < NWV; ++w) any |= s_cnt[w];
+            if (__builtin_amdgcn_readfirstlane(any) == 0) break;
+            enter();
+        }
     }
-#undef HZ_MOVE_J
     if (ph && tid == 0) ph[4] = wall_clock64();
 
     // 5. Theta rescale and write Z_tilde (column-major W2 x W2); the identity
-    // when nothing was transformed or swapped.  The groups hold columns 2 grp
-    // and 2 grp + 1.
+    // when nothing was transformed or swapped.
     __syncthreads();                         // s_cnt free
     if (lane == 0) {
         s_cnt[3 * wave] = n_all / LP;
@@ -519,18 +596,19 @@ __device__ __forceinline__ void ring_solve(double *__restrict__ sF, double *__re
     double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
 #pragma unroll
     for (int k = 0; k < RPL; ++k) {
-        a = fma(gi[k], gi[k], fma(fi[k], fi[k], a));
-        b = fma(gj[k], gj[k], fma(fj[k], fj[k], b));
+        a = fma(gx[k], gx[k], fma(fx[k], fx[k], a));
+        b = fma(gy[k], gy[k], fma(fy[k], fy[k], b));
     }
     group_sum4<GW>(a, b, c, d);
-    const double ti = rsqrt_nr(a), tj = rsqrt_nr(b);
+    const double tx = rsqrt_nr(a), ty = rsqrt_nr(b);
+    auto unit = [](bool p) { return p ? 1.0 : 0.0; };
 #pragma unroll
     for (int k = 0; k < RPL; k += 2) {
-        const int r = RI(k), c0 = 2 * grp;
-        const d2 one = d2{(r == c0) ? 1.0 : 0.0, (r + 1 == c0) ? 1.0 : 0.0};
-        const d2 two = d2{(r == c0 + 1) ? 1.0 : 0.0, (r == c0) ? 1.0 : 0.0};
-        *(d2 *)(zt + c0 * W2 + r) = changed ? d2{zi[k] * ti, zi[k + 1] * ti} : one;
-        *(d2 *)(zt + (c0 + 1) * W2 + r) = changed ? d2{zj[k] * tj, zj[k + 1] * tj} : two;
+        const int r = RI(k);
+        *(d2 *)(zt + cx * W2 + r) = changed ? d2{zx[k] * tx, zx[k + 1] * tx}
+                                            : d2{unit(r == cx), unit(r + 1 == cx)};
+        *(d2 *)(zt + cy * W2 + r) = changed ? d2{zy[k] * ty, zy[k + 1] * ty}
+                                            : d2{unit(r == cy), unit(r + 1 == cy)};
     }
     if (tid == 0) {
         myc[0] = ta;
@@ -551,25 +629,21 @@ __device__ __forceinline__ void ring_solve(double *__restrict__ sF, double *__re
 // which only renormalizes columns that already have ||f_j||^2 + ||g_j||^2 =
 // 1 up to rounding; it is then set to I exactly and myc[3] = 1, so the
 // block update may be skipped (Section 2.5).
-template <int W2, int LP, bool RING = false>
+template <int W2, int LP, int ORD, bool GEN>
 __device__ __forceinline__ void inner_solve(
     const double *__restrict__ pa, const double *__restrict__ pb, int nsplit, size_t sstride,
-    const int16_t *__restrict__ itab, int isteps, int inner_max, double tol, int sort, int variant,
-    double *__restrict__ zt, unsigned long long *__restrict__ myc, int *__restrict__ status,
+    int inner_max, double tol, int sort, int variant, double *__restrict__ zt, unsigned long long *__restrict__ myc, int *__restrict__ status,
     int failcode, unsigned long long *__restrict__ ph, double *__restrict__ lds)
 {
-    constexpr int W = W2 / 2;         // column pairs per inner step
-    constexpr int NT = W * LP;
-    constexpr int RPL = W2 / LP;      // rows per lane
-    constexpr int LDI = W2 + 2;
-    static_assert(RPL >= 2 && RPL % 2 == 0 && NT >= 64, "bad inner geometry");
+    constexpr int NT = (W2 / 2) * LP;
+    constexpr int LDI = inner_ld<W2>();
+    static_assert(NT >= 64, "bad inner geometry");
     double *const sF = lds;
     double *const sG = lds + W2 * LDI;
     double *const sZ = lds + 2 * W2 * LDI;
     double *const lbuf0 = lds + 3 * W2 * LDI;                 // 2 x 64 doubles
-    int16_t *const stab = (int16_t *)(lbuf0 + 128);           // W2 * W2 entries
-    unsigned *const s_cnt = (unsigned *)(lbuf0 + 128 + W2 * W2 / 4);
-    int *const s_failp = (int *)(s_cnt + 3 * W);
+    unsigned *const s_cnt = (unsigned *)(lbuf0 + 128);        // 3 words per wave
+    int *const s_failp = (int *)(s_cnt + 3 * (NT / 64));
 #define s_fail (*s_failp)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -599,7 +673,6 @@ __device__ __forceinline__ void inner_solve(
             *(d2 *)(sF + col * LDI + row) = va[it];
             *(d2 *)(sG + col * LDI + row) = vb[it];
         }
-        if (!RING) copy_table<NT>(stab, itab, isteps * W * 2);
         if (tid == 0) s_fail = 0;
     } else {
         for (int e = 2 * tid; e < W2 * W2; e += 2 * NT) {
@@ -614,7 +687,6 @@ __device__ __forceinline__ void inner_solve(
             *(d2 *)(sF + col * LDI + row) = a;
             *(d2 *)(sG + col * LDI + row) = b;
         }
-        if (!RING) copy_table<NT>(stab, itab, isteps * W * 2);
         if (tid == 0) s_fail = 0;
     }
     __syncthreads();
@@ -767,133 +839,7 @@ __device__ __forceinline__ void inner_solve(
         return;
     }
 
-    if constexpr (RING) {
-        ring_solve<W2, LP>(sF, sG, sZ, s_cnt, inner_max, tol, sort, variant, zt, myc, ph);
-        return;
-    }
-    const int grp = tid / LP, gl = tid % LP, r0 = gl * RPL;
-    // row k (0 <= k < RPL) of a lane's share of a column
-    auto RI = [&](int k) { return r0 + k; };
-    // 3. prescale the factor pair: columns 2*grp and 2*grp+1 per group.
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = 2 * grp + h;
-        double s = 0.0;
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const double g = sG[c * LDI + RI(r)];
-            s = fma(g, g, s);
-        }
-        s = dpp_group_sum<LP>(s);
-        const double d = rsqrt_nr(s);
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            sF[c * LDI + RI(r)] *= d;
-            sG[c * LDI + RI(r)] *= d;
-            sZ[c * LDI + RI(r)] = (RI(r) == c) ? d : 0.0;
-        }
-    }
-    __syncthreads();
-    if (ph && tid == 0) ph[3] = wall_clock64();
-
-    // 4. inner sweeps
-    const double tol2 = tol * tol;
-    unsigned my_all = 0, my_big = 0, my_chg = 0;
-    int nsw = 0;
-    auto load = [&](const double *M, int c, double (&x)[RPL]) {
-#pragma unroll
-        for (int r = 0; r < RPL; r += 2) {
-            const d2 v = *(const d2 *)(M + c * LDI + RI(r));
-            x[r] = v[0];
-            x[r + 1] = v[1];
-        }
-    };
-    auto store = [&](double *M, int c, const double (&x)[RPL]) {
-#pragma unroll
-        for (int r = 0; r < RPL; r += 2) *(d2 *)(M + c * LDI + RI(r)) = d2{x[r], x[r + 1]};
-    };
-    for (int sw = 0; sw < inner_max; ++sw) {
-        unsigned sw_all = 0, sw_big = 0;
-        ++nsw;
-        for (int st = 0; st < isteps; ++st) {
-            const int ci = stab[(st * W + grp) * 2], cj = stab[(st * W + grp) * 2 + 1];
-            double fi[RPL], fj[RPL], gi[RPL], gj[RPL], zi[RPL], zj[RPL];
-            load(sF, ci, fi);
-            load(sF, cj, fj);
-            load(sG, ci, gi);
-            load(sG, cj, gj);
-            load(sZ, ci, zi);
-            load(sZ, cj, zj);
-            double aii, ajj, aij, bij, z11, z21, z12, z22;
-            pair_dots<LP, RPL>(fi, fj, gi, gj, variant, aii, ajj, aij, bij);
-            bool rot, big;
-            const bool chg = pair_transform(aii, ajj, aij, bij, tol, tol2, sort, variant,
-                                            z11, z21, z12, z22, rot, big);
-            sw_all += rot;
-            sw_big += big;
-            if (chg) {
-                my_chg = 1;
-                rotate_rows<RPL>(fi, fj, z11, z21, z12, z22);
-                rotate_rows<RPL>(gi, gj, z11, z21, z12, z22);
-                rotate_rows<RPL>(zi, zj, z11, z21, z12, z22);
-                store(sF, ci, fi);
-                store(sF, cj, fj);
-                store(sG, ci, gi);
-                store(sG, cj, gj);
-                store(sZ, ci, zi);
-                store(sZ, cj, zj);
-            }
-            __syncthreads();
-        }
-        my_all += sw_all;
-        my_big += sw_big;
-        const int any = __builtin_amdgcn_readfirstlane(__syncthreads_count(gl == 0 && sw_all > 0));
-        if (any == 0) break;
-    }
-
-    if (ph && tid == 0) ph[4] = wall_clock64();
-    // 5. Theta rescale and write Z_tilde (column-major W2 x W2); the
-    // identity when nothing was transformed or swapped.
-    const int nchg =
-        __builtin_amdgcn_readfirstlane(__syncthreads_count(gl == 0 && my_chg != 0));
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = 2 * grp + h;
-        if (nchg == 0) {
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) zt[c * W2 + RI(r)] = (RI(r) == c) ? 1.0 : 0.0;
-            continue;
-        }
-        double s = 0.0;
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const double f = sF[c * LDI + RI(r)], g = sG[c * LDI + RI(r)];
-            s = fma(f, f, s);
-            s = fma(g, g, s);
-        }
-        s = dpp_group_sum<LP>(s);
-        const double th = rsqrt_nr(s);
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) zt[c * W2 + RI(r)] = sZ[c * LDI + RI(r)] * th;
-    }
-    // counters: the groups' totals summed in group order
-    if (gl == 0) {
-        s_cnt[3 * grp] = my_all;
-        s_cnt[3 * grp + 1] = my_big;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        unsigned long long ta = 0, tb = 0;
-        for (int g = 0; g < W; ++g) {
-            ta += s_cnt[3 * g];
-            tb += s_cnt[3 * g + 1];
-        }
-        myc[0] = ta;
-        myc[1] = tb;
-        myc[2] = (unsigned long long)nsw;
-        myc[3] = (nchg == 0) ? 1ull : 0ull;
-        if (ph) ph[5] = wall_clock64();
-    }
+    pointwise_solve<W2, LP, ORD, GEN>(sF, sG, sZ, s_cnt, inner_max, tol, sort, variant, zt, myc, ph);
 #undef s_fail
 }
 

@@ -118,28 +118,52 @@ __global__ __launch_bounds__(256) void k_gram_sum(const double *__restrict__ par
 //     wave); a non-positive pivot flags HZ_ECHOL.
 //  3. Z_hat = diag(1/||g_hat_j||), F_hat, G_hat scaled by it.
 //  4. Inner sweeps (<= inner_max, stop after a sweep without
-//     transformations): per step, the LP lanes of a column pair form a_ii,
-//     a_jj, a_ij, b_ij with DPP sums, then the skip test, the 2x2
-//     transformation, criterion C1, the sorting swap, applied in LDS.
+//     transformations), the columns in registers: per step, the LP lanes of
+//     a column pair form a_ii, a_jj, a_ij, b_ij, then the skip test, the 2x2
+//     transformation, criterion C1 and the sorting swap, and the columns pass
+//     on to the next step's pairs by lane exchanges or through LDS.
 //  5. Z_tilde = Z_hat Theta, Theta_jj = (||f_hat_j||^2+||g_hat_j||^2)^-1/2.
 // Counters per (step, pair): transformations, big ones, inner sweeps run.
 // ------------------------------------------------------------------------
-template <int W2, int LP, bool RING>
-__global__ __launch_bounds__((W2 / 2) * LP) void k_inner(
-    const double *__restrict__ gram, int nsplit, int npairs, int step,
-    const int16_t *__restrict__ itab, int isteps, int inner_max, double tol, int sort, int variant,
-    double *__restrict__ Zt, unsigned long long *__restrict__ cnt, int *__restrict__ status,
-    unsigned long long *__restrict__ phase)
+template <int W2, int LP, int ORD, bool GEN>
+__device__ __forceinline__ void inner_body(const double *gram, int nsplit, int npairs, int step,
+                                           int inner_max, double tol, int sort, int variant,
+                                           double *Zt, unsigned long long *cnt, int *status,
+                                           unsigned long long *phase)
 {
     const int pr = blockIdx.x;
     const int ns = nsplit > 0 ? nsplit : 1;   // nsplit 0: one triangular factor per matrix
     const double *pa = gram + (size_t)(pr * 2) * ns * (W2 * W2);
     __shared__ __attribute__((aligned(16))) double lds[inner_lds<W2>()];
-    inner_solve<W2, LP, RING>(pa, pa + (size_t)ns * (W2 * W2), nsplit, W2 * W2, itab, isteps,
-                        inner_max, tol, sort, variant,
-                        Zt + (size_t)pr * (W2 * W2), cnt + ((size_t)step * npairs + pr) * 4,
-                        status, step * 65536 + pr,
-                        phase ? phase + ((size_t)step * npairs + pr) * 8 : nullptr, lds);
+    inner_solve<W2, LP, ORD, GEN>(pa, pa + (size_t)ns * (W2 * W2), nsplit, W2 * W2, inner_max, tol,
+                                  sort, variant, Zt + (size_t)pr * (W2 * W2),
+                                  cnt + ((size_t)step * npairs + pr) * 4, status,
+                                  step * 65536 + pr,
+                                  phase ? phase + ((size_t)step * npairs + pr) * 8 : nullptr, lds);
+}
+
+// variant 0 with sorting, the default
+template <int W2, int LP, int ORD>
+__global__ __launch_bounds__((W2 / 2) * LP) void k_inner(
+    const double *__restrict__ gram, int nsplit, int npairs, int step, int inner_max, double tol,
+    int sort, int variant, double *__restrict__ Zt,
+    unsigned long long *__restrict__ cnt, int *__restrict__ status,
+    unsigned long long *__restrict__ phase)
+{
+    inner_body<W2, LP, ORD, false>(gram, nsplit, npairs, step, inner_max, tol, sort, variant,
+                                   Zt, cnt, status, phase);
+}
+
+// any variant, sorted or not
+template <int W2, int LP, int ORD>
+__global__ __launch_bounds__((W2 / 2) * LP) void k_inner_any(
+    const double *__restrict__ gram, int nsplit, int npairs, int step, int inner_max, double tol,
+    int sort, int variant, double *__restrict__ Zt,
+    unsigned long long *__restrict__ cnt, int *__restrict__ status,
+    unsigned long long *__restrict__ phase)
+{
+    inner_body<W2, LP, ORD, true>(gram, nsplit, npairs, step, inner_max, tol, sort, variant,
+                                  Zt, cnt, status, phase);
 }
 
 // ------------------------------------------------------------------------
@@ -323,7 +347,7 @@ __global__ __launch_bounds__(256) void k_eval_2x2(int64_t count, const double *_
     if (i >= count) return;
     const double aii = in[4 * i], ajj = in[4 * i + 1];
     double rb, qb, rs, rr, t;
-    hz_real_2x2_fast(aii, ajj, in[4 * i + 2], in[4 * i + 3], rb, qb, rs, rr, t);
+    hz_real_2x2_fast(aii, ajj, in[4 * i + 2], in[4 * i + 3], false, rb, qb, rs, rr, t);
     const bool less = aii < ajj;
     out[4 * i] = less ? rs : rb;
     out[4 * i + 1] = less ? rr : -qb;
@@ -423,13 +447,21 @@ void launch_prescale_real(const Plan &P, const Ptrs &W, const double *F, int64_t
                        ldg, P.nw, P.mfw, P.mgw, P.nzw, W.Fw, W.Gw, W.Zw, W.status);
 }
 
-template <int W2, int LP, bool RING>
+template <int W2, int LP>
 static void inner_launch(const Plan &P, const Ptrs &W, int step, const hz_params &prm,
                          double tol, const double *src, int ns, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_inner<W2, LP, RING>), dim3(P.npairs), dim3((W2 / 2) * LP), 0, s, src,
-                       ns, P.npairs, step, W.itab, P.isteps, prm.inner_max_sweeps, tol, prm.sort,
-                       prm.variant, W.Zt, W.cnt, W.status, W.phase);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(P.npairs), dim3((W2 / 2) * LP), 0, s, src, ns, P.npairs, step,
+                           prm.inner_max_sweeps, tol, prm.sort, prm.variant, W.Zt, W.cnt,
+                           W.status, W.phase);
+    };
+    const bool std = prm.variant == 0 && prm.sort;
+    switch (prm.inner_ordering) {
+    case HZ_ORD_MM: std ? go(k_inner<W2, LP, HZ_ORD_MM>) : go(k_inner_any<W2, LP, HZ_ORD_MM>); break;
+    case HZ_ORD_RR: std ? go(k_inner<W2, LP, HZ_ORD_RR>) : go(k_inner_any<W2, LP, HZ_ORD_RR>); break;
+    default: std ? go(k_inner<W2, LP, HZ_ORD_RING>) : go(k_inner_any<W2, LP, HZ_ORD_RING>); break;
+    }
 }
 
 template <int W2>
@@ -438,21 +470,12 @@ static void inner_impl(const Plan &P, const Ptrs &W, int step, const hz_params &
 {
     const double *src = partials ? W.part : W.gram;
     const int ns = partials ? P.splits : (prm.pivot_qr ? 0 : 1);
-    const bool ring = (prm.inner_ordering == HZ_ORD_RING);
     if constexpr (W2 == 16) {
-        if (ring) inner_launch<W2, 8, true>(P, W, step, prm, tol, src, ns, s);
-        else inner_launch<W2, 8, false>(P, W, step, prm, tol, src, ns, s);
+        inner_launch<W2, 8>(P, W, step, prm, tol, src, ns, s);
     } else {
-        if (P.inner_lp == 4) {
-            if (ring) inner_launch<W2, 4, true>(P, W, step, prm, tol, src, ns, s);
-            else inner_launch<W2, 4, false>(P, W, step, prm, tol, src, ns, s);
-        } else if (P.inner_lp == 8) {
-            if (ring) inner_launch<W2, 8, true>(P, W, step, prm, tol, src, ns, s);
-            else inner_launch<W2, 8, false>(P, W, step, prm, tol, src, ns, s);
-        } else {
-            if (ring) inner_launch<W2, 16, true>(P, W, step, prm, tol, src, ns, s);
-            else inner_launch<W2, 16, false>(P, W, step, prm, tol, src, ns, s);
-        }
+        if (P.inner_lp == 4) inner_launch<W2, 4>(P, W, step, prm, tol, src, ns, s);
+        else if (P.inner_lp == 8) inner_launch<W2, 8>(P, W, step, prm, tol, src, ns, s);
+        else inner_launch<W2, 16>(P, W, step, prm, tol, src, ns, s);
     }
 }
 
