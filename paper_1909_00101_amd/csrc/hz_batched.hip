@@ -246,14 +246,19 @@ __global__ __launch_bounds__((W2 / 2) * LP) void kb_persist(
     constexpr int LDSN = (L1 > L2 ? (L1 > L3 ? L1 : L3) : (L2 > L3 ? L2 : L3));
     __shared__ __attribute__((aligned(16))) double lds[LDSN];
     __shared__ unsigned long long c[4];
-    __shared__ int s_task, s_skip;
+    __shared__ int s_task[2], s_skip[2];
     const int tid = threadIdx.x, lane = tid & 63;
     // Claiming, waiting and deciding run on all lanes of wave 0 with every
     // value read made wave-uniform (readfirstlane), so that every branch of
     // the task loop is uniform: a loop exit taken by one lane alone would
     // let the compiler split the wave between loop levels.
     const bool claimer = __builtin_amdgcn_readfirstlane(tid >> 6) == 0;
-    for (;;) {
+    // The claimed task goes to the other waves through two slots taken in
+    // turn: after a skipped task wave 0 claims the next one at once, while a
+    // wave that the other workgroups of its SIMD hold up may not have read the
+    // last one yet.  It can be one claim behind, not two: the barrier below
+    // waits for it.
+    for (int slot = 0;; slot ^= 1) {
         if (claimer) {
             int t = 0;
             if (lane == 0) t = atomicAdd(qhead, 1);
@@ -308,14 +313,14 @@ __global__ __launch_bounds__((W2 / 2) * LP) void kb_persist(
                 }
             }
             if (lane == 0) {
-                s_task = t;
-                s_skip = skip;
+                s_task[slot] = t;
+                s_skip[slot] = skip;
             }
         }
         __syncthreads();
-        const int t = __builtin_amdgcn_readfirstlane(s_task);
+        const int t = __builtin_amdgcn_readfirstlane(s_task[slot]);
         if (t >= ntasks) break;
-        if (__builtin_amdgcn_readfirstlane(s_skip)) continue;
+        if (__builtin_amdgcn_readfirstlane(s_skip[slot])) continue;
         const int2 tk = tasks[t];
         const int i = __builtin_amdgcn_readfirstlane(tk.x);
         const int r = __builtin_amdgcn_readfirstlane(tk.y) >> 12;
