@@ -117,8 +117,8 @@ __global__ __launch_bounds__(256) void k_gram_sum(const double *__restrict__ par
 //     i, the new column of L broadcast through LDS (both matrices in one
 //     wave); a non-positive pivot flags HZ_ECHOL.
 //  3. Z_hat = diag(1/||g_hat_j||), F_hat, G_hat scaled by it.
-//  4. Inner sweeps (<= inner_max, stop after a sweep without
-//     transformations), the columns in registers: per step, the LP lanes of
+//  4. Inner sweeps (<= inner_max, stop after a sweep without big
+//     transformations, the rule of the outer sweeps), the columns in registers: per step, the LP lanes of
 //     a column pair form a_ii, a_jj, a_ij, b_ij, then the skip test, the 2x2
 //     transformation, criterion C1 and the sorting swap, and the columns pass
 //     on to the next step's pairs by lane exchanges or through LDS.

@@ -46,3 +46,20 @@ def test_inner_geometry(w, lanes, ordering, inner, sort):
                           inner_max_sweeps=1, max_sweeps=1, sort=sort, ordering=2)
             pairs = w * (2 * w - 1) if ordering != "mm" else 2 * w * w
             assert one["rot_total"] == pairs
+
+
+@pytest.mark.parametrize("ordering", ["rr", "ring"])
+def test_full_block_on_graded_columns(ordering):
+    """Sigma over twelve orders of magnitude: a transformation may be small
+    (criterion C1) and still turn the small column of a pair by much, and an
+    inner solve ends after a sweep of small ones.  U and V have to come out
+    orthonormal to the bound of the other tests, and the pencil diagonal."""
+    import paper_1909_00101_amd as hz
+    for w, n in ((16, 96), (32, 64)):
+        F, G, _ = gi.custom_pair(300, 280, n, kappa=10.0, sig_lo=1e-6, sig_hi=1e6, seed=w)
+        r = hz.gsvd(torch.from_numpy(F).cuda(), torch.from_numpy(G).cuda(), w=w,
+                    inner_ordering=ORDERINGS[ordering])
+        out = {k: r[k].cpu().numpy() for k in ("U", "V", "Z", "sigma", "sigma_f", "sigma_g")}
+        assert r["status"] == 0 and r["converged"]
+        assert_contract(F, G, out["U"], out["V"], out["Z"], out["sigma_f"], out["sigma_g"],
+                        out["sigma"], tol_res=1e-12, tol_orth=1e-12)
