@@ -6,8 +6,11 @@
 // block steps of Gram -> inner solve -> update, then extraction and sort.
 // Complex products on FP64 MFMA use four real products per complex
 // multiply-accumulate.  No floating-point atomics; fixed reduction orders.
+#include <type_traits>
+
 #include "hz_device.h"
 #include "hz_internal.h"
+#include "hz_pointwise.h"
 
 namespace hz {
 
@@ -209,25 +212,22 @@ __global__ __launch_bounds__(256) void k_gram_sum_z(const d2 *__restrict__ part,
 // pointwise method (Section 2.1.1), Theta rescale (Section 2.4).  Layout and
 // phases as the real k_inner; columns of F_hat, G_hat, Z_hat are
 // interleaved complex in LDS.
-template <int W2, int LP, bool RING>
+template <int W2, int LP, int ORD, bool GEN>
 __global__ __launch_bounds__((W2 / 2) * LP) void k_inner_z(
-    const d2 *__restrict__ gram, int factors, int npairs, int step,
-    const int16_t *__restrict__ itab, int isteps, int inner_max, double tol, int sort, int variant,
-    d2 *__restrict__ Zt, unsigned long long *__restrict__ cnt, int *__restrict__ status,
-    unsigned long long *__restrict__ phase)
+    const d2 *__restrict__ gram, int factors, int npairs, int step, int inner_max, double tol,
+    int sort, int variant, d2 *__restrict__ Zt, unsigned long long *__restrict__ cnt,
+    int *__restrict__ status, unsigned long long *__restrict__ phase)
 {
     constexpr int W = W2 / 2;
     constexpr int NT = W * LP;
-    constexpr int RPL = W2 / LP;
     constexpr int LDI = W2 + 1;
-    static_assert(RPL >= 1 && NT >= 64 && W2 <= 32, "bad complex inner geometry");
+    static_assert(NT >= 64 && W2 <= 32, "bad complex inner geometry");
     __shared__ d2 sF[W2 * LDI];
     __shared__ d2 sG[W2 * LDI];
     __shared__ d2 sZ[W2 * LDI];
-    __shared__ int16_t stab[W2 * W2];
     __shared__ d2 lbuf[2][32];
     __shared__ int s_fail;
-    __shared__ unsigned s_cnt[2 * W];
+    __shared__ unsigned s_cnt[3 * (NT / 64)];
 
     const int pr = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     unsigned long long *myc = cnt + ((size_t)step * npairs + pr) * 4;
@@ -254,7 +254,6 @@ __global__ __launch_bounds__((W2 / 2) * LP) void k_inner_z(
             sF[col * LDI + row] = va[it];
             sG[col * LDI + row] = vb[it];
         }
-        if (!RING) copy_table<NT>(stab, itab, isteps * W * 2);   // the ring needs no table
         if (tid == 0) s_fail = 0;
     }
     __syncthreads();
@@ -326,228 +325,9 @@ __global__ __launch_bounds__((W2 / 2) * LP) void k_inner_z(
         return;
     }
 
-    const int grp = tid / LP, gl = tid % LP, r0 = gl * RPL;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = 2 * grp + h;
-        double s = 0.0;
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const d2 g = sG[c * LDI + r0 + r];
-            s = fma(g[0], g[0], fma(g[1], g[1], s));
-        }
-        s = dpp_group_sum<LP>(s);
-        const double d = rsqrt_nr(s);
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            sF[c * LDI + r0 + r] *= d;
-            sG[c * LDI + r0 + r] *= d;
-            sZ[c * LDI + r0 + r] = (r0 + r == c) ? d2{d, 0.0} : d2{0.0, 0.0};
-        }
-    }
-    __syncthreads();
-    if (ph && tid == 0) ph[3] = wall_clock64();
-
-    const double tol2 = tol * tol;
-    unsigned my_all = 0, my_big = 0, my_chg = 0;
-    int nsw = 0;
-    for (int sw = 0; sw < inner_max; ++sw) {
-        unsigned sw_all = 0, sw_big = 0;
-        ++nsw;
-        // One pointwise step on column pair (i, j), i < j, held in registers:
-        // the complex pivot entries, the orthogonality test, the 2x2
-        // transformation of Section 2.1.1, criterion C1 (C2), the sorting
-        // swap, and [y_i y_j] <- [y_i y_j] Z' applied to the arrays.  Returns
-        // whether the columns changed.
-        auto pair_step = [&](d2 (&fi)[RPL], d2 (&fj)[RPL], d2 (&gi)[RPL], d2 (&gj)[RPL],
-                             d2 (&zi)[RPL], d2 (&zj)[RPL]) -> bool {
-            double aii = 0.0, ajj = 0.0, ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0;
-            if (variant & 1) {
-                // variants 1 and 5: squared norms by the enhanced procedure
-                // of Appendix A (the off-diagonal entries stay ordinary)
-#pragma unroll
-                for (int r = 0; r < RPL; ++r) {
-                    aii += enh_abs2(fi[r][0], fi[r][1]);
-                    ajj += enh_abs2(fj[r][0], fj[r][1]);
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < RPL; ++r) {
-                    aii = fma(fi[r][0], fi[r][0], fma(fi[r][1], fi[r][1], aii));
-                    ajj = fma(fj[r][0], fj[r][0], fma(fj[r][1], fj[r][1], ajj));
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                ar = fma(fi[r][0], fj[r][0], fma(fi[r][1], fj[r][1], ar));
-                ai = fma(fi[r][0], fj[r][1], fma(-fi[r][1], fj[r][0], ai));
-                br = fma(gi[r][0], gj[r][0], fma(gi[r][1], gj[r][1], br));
-                bi = fma(gi[r][0], gj[r][1], fma(-gi[r][1], gj[r][0], bi));
-            }
-            aii = dpp_group_sum<LP>(aii);
-            ajj = dpp_group_sum<LP>(ajj);
-            ar = dpp_group_sum<LP>(ar);
-            ai = dpp_group_sum<LP>(ai);
-            br = dpp_group_sum<LP>(br);
-            bi = dpp_group_sum<LP>(bi);
-            double z11 = 1.0, z22 = 1.0, z21r = 0.0, z21i = 0.0, z12r = 0.0, z12i = 0.0;
-            bool swap;
-            const bool orth = (fma(ar, ar, ai * ai) < aii * ajj * tol2) &&
-                              (fma(br, br, bi * bi) < tol2);
-            if (orth) {
-                swap = sort && (aii < ajj);
-            } else {
-                bool c2small;
-                hz_cplx_2x2_fast(aii, ajj, ar, ai, br, bi, z11, z21r, z21i, z12r, z12i, z22,
-                                 c2small);
-                sw_all += 1;
-                // small: criterion C1 (variants 0, 1) or C2 (variants 4, 5), Section 2.5
-                if ((variant & 4) ? !c2small : !(z11 == 1.0 && z22 == 1.0)) sw_big += 1;
-                swap = false;
-                if (sort) {
-                    // diagonal of Z^H A Z
-                    const double a11 = fma(z11 * z11, aii,
-                                           fma(2.0 * z11, fma(ar, z21r, -ai * z21i),
-                                               fma(z21r, z21r, z21i * z21i) * ajj));
-                    const double a22 = fma(fma(z12r, z12r, z12i * z12i), aii,
-                                           fma(2.0 * z22, fma(z12r, ar, z12i * ai),
-                                               z22 * z22 * ajj));
-                    swap = a11 < a22;
-                }
-            }
-            if (!(!orth || swap)) return false;
-            my_chg = 1;
-            // [y_i y_j] <- [y_i y_j] Z (z11, z22 real), then the sorting swap
-            auto rot = [&](d2 &yi, d2 &yj) {
-                d2 a, b;
-                a[0] = fma(yi[0], z11, fma(yj[0], z21r, -yj[1] * z21i));
-                a[1] = fma(yi[1], z11, fma(yj[0], z21i, yj[1] * z21r));
-                b[0] = fma(yj[0], z22, fma(yi[0], z12r, -yi[1] * z12i));
-                b[1] = fma(yj[1], z22, fma(yi[0], z12i, yi[1] * z12r));
-                yi = swap ? b : a;
-                yj = swap ? a : b;
-            };
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) {
-                rot(fi[r], fj[r]);
-                rot(gi[r], gj[r]);
-                rot(zi[r], zj[r]);
-            }
-            return true;
-        };
-        auto load = [&](const d2 *M, int c, d2 (&x)[RPL]) {
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) x[r] = M[c * LDI + r0 + r];
-        };
-        auto store = [&](d2 *M, int c, const d2 (&x)[RPL]) {
-#pragma unroll
-            for (int r = 0; r < RPL; ++r) M[c * LDI + r0 + r] = x[r];
-        };
-        if constexpr (RING) {
-            // the ring ordering of the real solver (HZ_ORD_RING): the first
-            // column of a pair stays in registers for a level, the second
-            // half of the block is visited in-wave between phase barriers
-            constexpr int GW = 64 / LP;
-            for (int h = W; h >= 1; h >>= 1) {
-                const int blk = grp / h, u = grp % h;
-                const int ci = blk * 2 * h + u;
-                const int nset = (h >= GW) ? h / GW : 1, ssz = (h >= GW) ? GW : h;
-                const int ow = u / ssz, gw = u % ssz;
-                d2 fi[RPL], gi[RPL], zi[RPL];
-                load(sF, ci, fi);
-                load(sG, ci, gi);
-                load(sZ, ci, zi);
-                for (int p = 0; p < nset; ++p) {
-                    for (int t = 0; t < ssz; ++t) {
-                        const int cj = blk * 2 * h + h + ring_col(ssz, nset, ow, gw, p, t);
-                        d2 fj[RPL], gj[RPL], zj[RPL];
-                        load(sF, cj, fj);
-                        load(sG, cj, gj);
-                        load(sZ, cj, zj);
-                        if (pair_step(fi, fj, gi, gj, zi, zj)) {
-                            store(sF, cj, fj);
-                            store(sG, cj, gj);
-                            store(sZ, cj, zj);
-                        }
-                        if (t + 1 < ssz) wave_fence();
-                    }
-                    __syncthreads();
-                }
-                store(sF, ci, fi);
-                store(sG, ci, gi);
-                store(sZ, ci, zi);
-                __syncthreads();
-            }
-        } else {
-            for (int st = 0; st < isteps; ++st) {
-                const int ci = stab[(st * W + grp) * 2], cj = stab[(st * W + grp) * 2 + 1];
-                d2 fi[RPL], fj[RPL], gi[RPL], gj[RPL], zi[RPL], zj[RPL];
-                load(sF, ci, fi);
-                load(sF, cj, fj);
-                load(sG, ci, gi);
-                load(sG, cj, gj);
-                load(sZ, ci, zi);
-                load(sZ, cj, zj);
-                if (pair_step(fi, fj, gi, gj, zi, zj)) {
-                    store(sF, ci, fi);
-                    store(sF, cj, fj);
-                    store(sG, ci, gi);
-                    store(sG, cj, gj);
-                    store(sZ, ci, zi);
-                    store(sZ, cj, zj);
-                }
-                __syncthreads();
-            }
-        }
-        my_all += sw_all;
-        my_big += sw_big;
-        const int any = __syncthreads_count(gl == 0 && sw_all > 0);
-        if (any == 0) break;
-    }
-
-    if (ph && tid == 0) ph[4] = wall_clock64();
-    // Z_tilde = Z_hat Theta, or exactly I when nothing was transformed or
-    // swapped (the block update is then skipped, Section 2.5)
-    d2 *zt = Zt + (size_t)pr * (W2 * W2);
-    const int nchg = __syncthreads_count(gl == 0 && my_chg != 0);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = 2 * grp + h;
-        if (nchg == 0) {
-#pragma unroll
-            for (int r = 0; r < RPL; ++r)
-                zt[c * W2 + r0 + r] = d2{(r0 + r == c) ? 1.0 : 0.0, 0.0};
-            continue;
-        }
-        double s = 0.0;
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) {
-            const d2 f = sF[c * LDI + r0 + r], g = sG[c * LDI + r0 + r];
-            s = fma(f[0], f[0], fma(f[1], f[1], s));
-            s = fma(g[0], g[0], fma(g[1], g[1], s));
-        }
-        s = dpp_group_sum<LP>(s);
-        const double th = rsqrt_nr(s);
-#pragma unroll
-        for (int r = 0; r < RPL; ++r) zt[c * W2 + r0 + r] = sZ[c * LDI + r0 + r] * th;
-    }
-    if (gl == 0) {
-        s_cnt[2 * grp] = my_all;
-        s_cnt[2 * grp + 1] = my_big;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        unsigned long long ta = 0, tb = 0;
-        for (int g = 0; g < W; ++g) {
-            ta += s_cnt[2 * g];
-            tb += s_cnt[2 * g + 1];
-        }
-        myc[0] = ta;
-        myc[1] = tb;
-        myc[2] = (unsigned long long)nsw;
-        myc[3] = (nchg == 0) ? 1ull : 0ull;
-        if (ph) ph[5] = wall_clock64();
-    }
+    pointwise_solve<CplxCols, W2, LP, ORD, GEN>((double *)sF, (double *)sG, (double *)sZ, s_cnt,
+                                                inner_max, tol, sort, variant,
+                                                (double *)(Zt + (size_t)pr * (W2 * W2)), myc, ph);
 }
 
 // Complex block update [Y_p Y_q] <- [Y_p Y_q] Z_tilde in place
@@ -734,9 +514,17 @@ __global__ __launch_bounds__(256) void k_eval_2x2_z(int64_t count, const double 
     if (i >= count) return;
     const double *a = in + 6 * i;
     double *o = out + 6 * i;
-    bool c2small;
-    hz_cplx_2x2_fast(a[0], a[1], a[2], a[3], a[4], a[5], o[0], o[1], o[2], o[3], o[4], o[5],
-                     c2small);
+    const bool less = a[0] < a[1];           // b is the second column
+    const double sg = less ? -1.0 : 1.0;
+    double rb, cbr, cbi, rs, csr, csi, t;
+    hz_cplx_2x2_fast(less ? a[1] : a[0], less ? a[0] : a[1], a[2], sg * a[3], a[4], sg * a[5],
+                     false, rb, cbr, cbi, rs, csr, csi, t);
+    o[0] = less ? rs : rb;
+    o[1] = less ? csr : cbr;
+    o[2] = less ? csi : cbi;
+    o[3] = less ? cbr : csr;
+    o[4] = less ? cbi : csi;
+    o[5] = less ? rb : rs;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -768,19 +556,28 @@ static void step_impl_z(const Plan &P, const Ptrs &W, int step, const hz_params 
     }
     prof_mark(K_GRAM, false, s);
     prof_mark(K_INNER, true, s);
-    const bool ring = (prm.inner_ordering == HZ_ORD_RING);
     auto go = [&](auto kern, int lp) {
         hipLaunchKernelGGL(kern, dim3(P.npairs), dim3((W2 / 2) * lp), 0, s, (const d2 *)W.gram,
-                           fac, P.npairs, step, W.itab, P.isteps, prm.inner_max_sweeps, tol,
-                           prm.sort, prm.variant, (d2 *)W.Zt, W.cnt, W.status, W.phase);
+                           fac, P.npairs, step, prm.inner_max_sweeps, tol, prm.sort, prm.variant,
+                           (d2 *)W.Zt, W.cnt, W.status, W.phase);
     };
-    if (W2 == 32 && P.inner_lp == 16) {
-        if (ring) go(k_inner_z<W2, 16, true>, 16);
-        else go(k_inner_z<W2, 16, false>, 16);
-    } else {
-        if (ring) go(k_inner_z<W2, 8, true>, 8);
-        else go(k_inner_z<W2, 8, false>, 8);
-    }
+    auto pick = [&](auto lp_c) {
+        constexpr int LP = decltype(lp_c)::value;
+        const bool std = prm.variant == 0 && prm.sort;
+        switch (prm.inner_ordering) {
+        case HZ_ORD_MM:
+            std ? go(k_inner_z<W2, LP, HZ_ORD_MM, false>, LP) : go(k_inner_z<W2, LP, HZ_ORD_MM, true>, LP);
+            break;
+        case HZ_ORD_RR:
+            std ? go(k_inner_z<W2, LP, HZ_ORD_RR, false>, LP) : go(k_inner_z<W2, LP, HZ_ORD_RR, true>, LP);
+            break;
+        default:
+            std ? go(k_inner_z<W2, LP, HZ_ORD_RING, false>, LP) : go(k_inner_z<W2, LP, HZ_ORD_RING, true>, LP);
+            break;
+        }
+    };
+    if (W2 == 32 && P.inner_lp == 16) pick(std::integral_constant<int, W2 == 32 ? 16 : 8>());
+    else pick(std::integral_constant<int, 8>());
     prof_mark(K_INNER, false, s);
     const int64_t rpt = 4 * (int64_t)P.upd_rows;
     const int nt = (int)((P.mfw + P.mgw + P.nzw + rpt - 1) / rpt);

@@ -115,6 +115,21 @@ __device__ __forceinline__ void group_sum4(double &s1, double &s2, double &s3, d
     swap32(s3, s4);
 }
 
+// The same for two values (15 instructions).
+template <int GW>
+__device__ __forceinline__ void group_sum2(double &s1, double &s2)
+{
+    swap32(s1, s2);
+    double u = s1 + s2;                      // lower half: s1; upper: s2
+    double v = u;
+    swap16(u, v);
+    u += v;
+    if (GW <= 8) u += dpp_d<0x128>(u);       // row_ror:8
+    if (GW <= 4) u += dpp_d<0x124>(u);       // row_ror:4
+    s1 = s2 = u;
+    swap32(s1, s2);
+}
+
 // Broadcast lane l's double to the wave (two v_readlane_b32; l uniform).
 __device__ __forceinline__ double readlane_d(double v, int l)
 {
@@ -122,24 +137,6 @@ __device__ __forceinline__ double readlane_d(double v, int l)
     const int lo = __builtin_amdgcn_readlane((int)b, l);
     const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
-
-// Copy n int16 entries (the inner ordering table) from global memory to
-// LDS with a workgroup of NT threads, four loads of a thread in flight
-// before its stores.
-template <int NT>
-__device__ __forceinline__ void copy_table(int16_t *__restrict__ dst, const int16_t *__restrict__ src,
-                                           int n)
-{
-    const int tid = threadIdx.x;
-    for (int e0 = tid; e0 < n; e0 += 4 * NT) {
-        int16_t v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = (e0 + k * NT < n) ? src[e0 + k * NT] : (int16_t)0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (e0 + k * NT < n) dst[e0 + k * NT] = v[k];
-    }
 }
 
 // Reciprocal square root from the hardware estimate y0 = v_rsq_f64(x)
@@ -238,76 +235,60 @@ __device__ __forceinline__ void hz_real_2x2_fast(double aii, double ajj, double 
     t = t2 * rt;
 }
 
-// The complex 2x2 transformation of Section 2.1.1 without infinities, for
-// A' = [[aii, a], [conj(a), ajj]], B' = [[1, b], [conj(b), 1]], |b| < 1.
-// x = |b|, e^{i zeta} = b/|b| (1 for b = 0), z = e^{-i zeta} a = u + i v,
-// h = ajj - aii, tau = sign(1, h), s = aii + ajj, t = sqrt(1 - x^2).
-// With P = tau (2u - s x), R = sqrt(h^2 + 4 v^2) and Q = t R,
-// tan 2theta = P / Q gives cos 2theta = Q / sqrt(P^2 + Q^2) and
-// sin 2theta = P / sqrt(P^2 + Q^2); tan gamma = 2v / h gives cos gamma =
-// |h| / R and sin gamma = tau 2v / R (so h = 0, v != 0 yields cos 0 and
-// sin = sign(v)).  Then, as printed,
-//   cos phi = sqrt((1 + x s2 + t cg c2) / 2), cos psi = sqrt((1 - x s2 + t cg c2) / 2),
-//   e^{i alpha} sin phi = e^{i zeta} ((s2 - x) + i t sg c2) / (2 cos psi),
-//   e^{-i beta} sin psi = e^{-i zeta} ((s2 + x) - i t sg c2) / (2 cos phi),
-// and Z' = (1/t)[[cos phi, e^{ia} sin phi], [-e^{-ib} sin psi, cos psi]].
-// The exception v = h = 0 returns the printed congruence.  Cosines that
-// round to 1 are exactly 1 (criterion C1).  Output: z11, z22 real; z21 =
-// (z21r, z21i), z12 = (z12r, z12i) (column-major Z).
-__device__ __forceinline__ void hz_cplx_2x2_fast(double aii, double ajj, double ar, double ai,
-                                                 double br, double bi, double &z11,
-                                                 double &z21r, double &z21i, double &z12r,
-                                                 double &z12i, double &z22, bool &c2small)
+// The complex 2x2 transformation of Section 2.1.1 in the form of the real one:
+// b the column with the larger diagonal entry, s the other, a = f_b^H f_s,
+// beta = g_b^H g_s, x = |beta| < 1, t = sqrt(1 - x^2), h = a_bb - a_ss >= 0;
+//     b'' = rb b + cb s,   s'' = rs s + cs b,   rb, rs > 0 real.
+// With D = 2a - (a_bb + a_ss) beta and m = Im(a conj(beta)), the coefficient
+// of b in s'' before scaling is the root
+//     r = 2 (a_ss beta - a) / (h + sqrt(t^2 h^2 + |D|^2 - 4 m^2) + 2 i m),
+// |r| <= 1, of the quadratic that makes the columns A'-orthogonal, and
+// B'-orthogonality gives the other one: with w = r + beta, o = 1 + conj(r) beta,
+// n_s = |w|^2 + t^2,
+//     rs = n_s^(-1/2), cs = r rs, rb = |o| rs / t, cb = -conj(w o) rs / (t |o|).
+// Eliminating the printed angles gives the same entries (their cosines divided
+// by t are rb, rs); with u + i v = e^(-i zeta) a the printed radicand t^2 (h^2 +
+// 4 v^2) + (2u - (a_bb + a_ss) x)^2 is the one above.  A' proportional to B'
+// takes r = -e^(i zeta) (-1 for beta = 0), the printed congruence; with keep (a =
+// beta = 0 passed) r = 0, the identity.
+__device__ __forceinline__ void hz_cplx_2x2_fast(double abb, double ass, double ar, double ai,
+                                                 double br, double bi, bool keep, double &rb,
+                                                 double &cbr, double &cbi, double &rs, double &csr,
+                                                 double &csi, double &t)
 {
-    const double x2 = fma(br, br, bi * bi);
-    const bool bz = (x2 == 0.0);
-    const double rx = bz ? 0.0 : rsqrt_nr(x2);
-    const double x = x2 * rx;
-    const double er = bz ? 1.0 : br * rx, ei = bz ? 0.0 : bi * rx;   // e^{i zeta}
-    const double u = fma(er, ar, ei * ai), v = fma(er, ai, -ei * ar);  // e^{-i zeta} a
-    const double h = ajj - aii;
-    const double t2 = fma(-x, x, 1.0);
-    const double rt = rsqrt_nr(t2);
-    const double t = t2 * rt;
-    if (v == 0.0 && h == 0.0) {
-        const double r2 = 0.70710678118654752440;
-        const double p = r2 * rsqrt_nr(1.0 + x), q = r2 * rsqrt_nr(1.0 - x);
-        z11 = p;
-        z21r = er * p;
-        z21i = -ei * p;
-        z12r = -er * q;
-        z12i = -ei * q;
-        z22 = q;
-        c2small = false;
-        return;
+    const double x2 = fma(br, br, bi * bi), t2 = 1.0 - x2;
+    const double h = abb - ass, S = abb + ass;
+    const double Dr = fma(-S, br, ar + ar), Di = fma(-S, bi, ai + ai);
+    const double m = fma(ai, br, -ar * bi), m2 = m + m;
+    const double hyp2 = fma(-m2, m2, fma(t2 * h, h, fma(Dr, Dr, Di * Di)));
+    const double nr = fma(ass, br, -ar), ni = fma(ass, bi, -ai);
+    const double p = h + sqrt_nr(hyp2);
+    const double q = fma(p, p, m2 * m2);                     // |denominator|^2
+    const double y0 = __builtin_amdgcn_rcp(q);
+    const double e = fma(-q, y0, 1.0);
+    const double y = fma(y0, fma(e, e, e), y0);
+    const double k2 = y + y;
+    const bool reg = hyp2 > 0.0;
+    double rr = k2 * fma(nr, p, ni * m2), ri = k2 * fma(ni, p, -nr * m2);
+    if (!reg) {
+        // A' proportional to B', a pair left alone, or a radicand lost to rounding
+        const double ix = (x2 > 0.0) ? rsqrt_nr(x2) : 0.0;
+        rr = keep ? 0.0 : (x2 > 0.0 ? -br * ix : -1.0);
+        ri = keep ? 0.0 : -bi * ix;
     }
-    const double tau = (h < 0.0) ? -1.0 : 1.0;
-    const double h2 = h * h, v4 = 4.0 * v * v;
-    const double R2 = h2 + v4;
-    const double rR = rsqrt_nr(R2);
-    const double cg = (R2 == h2) ? 1.0 : fabs(h) * rR;
-    const double sg = tau * 2.0 * v * rR;
-    const double P = tau * fma(-(aii + ajj), x, 2.0 * u);
-    const double Q2 = t2 * R2;
-    const double PQ = fma(P, P, Q2);
-    const double rPQ = rsqrt_nr(PQ);
-    const double c2 = (PQ == Q2) ? 1.0 : sqrt_nr(Q2) * rPQ;
-    const double s2 = P * rPQ;
-    const double tcc = t * cg * c2;
-    const double cphi = sqrt_nr(0.5 * (fma(x, s2, 1.0) + tcc));
-    const double cpsi = sqrt_nr(0.5 * (fma(-x, s2, 1.0) + tcc));
-    const double im = t * sg * c2;
-    const double dpsi = div_nr(rt, 2.0 * cpsi), dphi = div_nr(rt, 2.0 * cphi);
-    // e^{i zeta} ((s2 - x) + i im) / (2 cos psi) / t
-    const double ar_ = s2 - x, br_ = s2 + x;
-    z12r = (er * ar_ - ei * im) * dpsi;
-    z12i = (er * im + ei * ar_) * dpsi;
-    // -e^{-i zeta} ((s2 + x) - i im) / (2 cos phi) / t
-    z21r = -(er * br_ - ei * im) * dphi;
-    z21i = -(-er * im - ei * br_) * dphi;
-    z11 = cphi * rt;
-    z22 = cpsi * rt;
-    c2small = (cphi == 1.0 && cpsi == 1.0);     // criterion C2 (Section 2.5)
+    const double wr = rr + br, wi = ri + bi;
+    const double orr = fma(rr, br, fma(ri, bi, 1.0)), oi = fma(rr, bi, -ri * br);
+    const double rt = rsqrt_nr(t2);
+    rs = rsqrt_nr(fma(wr, wr, fma(wi, wi, t2)));
+    const double o2 = fma(orr, orr, oi * oi);
+    const double k = rt * rs * rsqrt_nr(o2);
+    csr = rr * rs;
+    csi = ri * rs;
+    rb = o2 * k;
+    // -conj(w) conj(o) k
+    cbr = -k * fma(wr, orr, -wi * oi);
+    cbi = k * fma(wr, oi, wi * orr);
+    t = t2 * rt;
 }
 
 // Appendix A (enhanced dot products): a*b rounded toward -infinity, from the
