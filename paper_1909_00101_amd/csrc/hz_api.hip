@@ -118,12 +118,13 @@ static int inner_table_kind(int inner_ordering)
 // columns, so more waves win); 2w = 64 72.1 against 68.5 in round robin, but 46.4
 // against 53.2 in the ring ordering, which moves columns between lanes and
 // whose second wave per SIMD would only repeat the 2x2 transformations.  2w = 16
-// has 8 column pairs: 8 lanes make one wave.
-static int inner_lanes_for(const hz_params &prm, int W2, int is_complex)
+// has 8 column pairs: 8 lanes make one wave.  Complex 2w = 32 (twice the
+// products per lane): 28.8 against 20.3 us of inner sweeps in the ring ordering
+// of the 3072/2048 x 1024 pair.
+static int inner_lanes_for(const hz_params &prm, int W2)
 {
     if (W2 == 16) return 8;
     if (prm.inner_lanes) return prm.inner_lanes;
-    if (is_complex) return 8;
     return (W2 == 64 && prm.inner_ordering == HZ_ORD_RING) ? 8 : 16;
 }
 
@@ -158,7 +159,7 @@ static bool make_plan(const hz_params &prm, int64_t mf, int64_t mg, int64_t n, i
     // sequence): 48 gives the real FP64 update of the 4096x1024 pair three
     // workgroups per compute unit
     P.upd_rows = prm.update_rows ? prm.update_rows : 48;
-    P.inner_lp = inner_lanes_for(prm, P.W2, is_complex);
+    P.inner_lp = inner_lanes_for(prm, P.W2);
     const size_t es = P.esz;
     size_t o = 0;
     P.o_fw = o; o = align256(o + es * (size_t)P.mfw * P.nw);
@@ -1305,7 +1306,7 @@ static bool plan_batched(const hz_params &prm, int batch, const int64_t *mf, con
     q.w = L.w;
     L.W2 = 2 * L.w;
     L.isteps = (prm.inner_ordering == HZ_ORD_MM) ? L.W2 : L.W2 - 1;
-    L.inner_lp = inner_lanes_for(prm, L.W2, 0);
+    L.inner_lp = inner_lanes_for(prm, L.W2);
     // The persistent schedule (default where it applies) runs a task's
     // inner solve with the whole workgroup of at least four waves: 2w = 64
     // with 8 or 16 lanes per column pair, 2w = 32 with 16.

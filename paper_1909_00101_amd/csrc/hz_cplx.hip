@@ -225,7 +225,7 @@ __global__ __launch_bounds__((W2 / 2) * LP) void k_inner_z(
     __shared__ d2 sF[W2 * LDI];
     __shared__ d2 sG[W2 * LDI];
     __shared__ d2 sZ[W2 * LDI];
-    __shared__ d2 lbuf[2][32];
+    __shared__ d2 lbuf[2][2][32];
     __shared__ int s_fail;
     __shared__ unsigned s_cnt[3 * (NT / 64)];
 
@@ -259,21 +259,79 @@ __global__ __launch_bounds__((W2 / 2) * LP) void k_inner_z(
     __syncthreads();
     if (ph && tid == 0) ph[1] = wall_clock64();
 
-    // Hermitian Cholesky, lane = row, A in lanes 0..31 and B in 32..63 of wave 0.
-    // With `factors` the blocks are already the upper triangular factors (QR
-    // of the block-column pairs, real diagonal): only the diagonals are
-    // checked for zeros and non-finite values.
+    // Hermitian Cholesky A_hat = L L^H.  With `factors` the blocks are already
+    // the upper triangular factors (QR of the block-column pairs, real
+    // diagonal): only the diagonals are checked for zeros and non-finite
+    // values.
     if (factors) {
         if (tid < W2) {
             const double df = sF[tid * LDI + tid][0], dg = sG[tid * LDI + tid][0];
             if (!(fabs(df) > 0.0 && fabs(df) < INFINITY && fabs(dg) > 0.0 && fabs(dg) < INFINITY))
                 s_fail = 1;
         }
+    } else if constexpr (W2 == 32) {
+        // One wave per matrix, lane = (row, half): the half h of a row holds its
+        // columns h, h + 2, h + 4, ..., so that the rank-1 update of a column
+        // takes half the instructions of a lane per row.  A new column reaches
+        // the other half by lane swaps and the rows' entries that scale it
+        // come back from LDS, two buffers in turn.  Bound: the chain of 32
+        // columns (pivot, reciprocal root, scaling, LDS, first update); with
+        // both matrices in one wave the updates, 496 broadcast loads and four
+        // times as many products, came on top.
+        if (wave < 2) {
+            d2 *M = wave ? sG : sF;
+            const int i = lane & 31, h = lane >> 5;
+            d2 a[W2 / 2];
+#pragma unroll
+            for (int u = 0; u < W2 / 2; ++u) a[u] = M[(2 * u + h) * LDI + i];
+            const double d0 = M[i * LDI + i][0];   // column i's diagonal before the factorization
+            double own = 1.0;                        // the pivot of column i, kept by lanes i, i + 32
+#pragma unroll
+            for (int j = 0; j < W2; ++j) {
+                const int u = j >> 1;
+                const double piv = readlane_d(a[u][0], j + 32 * (j & 1));
+                if (i == j) own = piv;
+                const double inv = rsqrt_nr(piv);
+                // column j in both halves
+                double xr = a[u][0], xi = a[u][1], yr = xr, yi = xi;
+                swap32(xr, yr);
+                swap32(xi, yi);
+                const double cr = (j & 1) ? yr : xr, ci = (j & 1) ? yi : xi;
+                d2 l = (i > j) ? d2{cr * inv, ci * inv} : d2{0.0, 0.0};
+                if (i == j) l = d2{piv * inv, 0.0};
+                if (h == (j & 1)) a[u] = l;
+                d2 *const lb = lbuf[wave][j & 1];
+                lb[i] = l;                           // both halves write the same
+                wave_fence();
+#pragma unroll
+                for (int v = (j + 1) >> 1; v < W2 / 2; ++v) {
+                    // column 2v + h; for odd j + 1 = 2v + 1 the lower half's 2v is done
+                    const d2 lk = lb[2 * v + h];
+                    const bool skip = 2 * v + h <= j;
+                    const double kr = skip ? 0.0 : lk[0], ki = skip ? 0.0 : lk[1];
+                    // a -= l * conj(lk)
+                    a[v][0] = fma(-l[0], kr, fma(-l[1], ki, a[v][0]));
+                    a[v][1] = fma(-l[1], kr, fma(l[0], ki, a[v][1]));
+                }
+            }
+            // F_hat = L^H: column i of F_hat is the conjugate of row i of L.
+            wave_fence();
+#pragma unroll
+            for (int u = 0; u < W2 / 2; ++u) {
+                const int k = 2 * u + h;
+                M[i * LDI + k] = (k <= i) ? d2{a[u][0], -a[u][1]} : d2{0.0, 0.0};
+            }
+            // numerically positive definite: every pivot above W2 * eps times
+            // its column's diagonal, each tested by the lane that holds it
+            if (!((own > W2 * 2.220446049250313e-16 * d0) && (own < INFINITY))) s_fail = 1;
+        }
     } else {
+        // 2w = 16: A in lanes 0..31 and B in 32..63 of wave 0, lane = row, the
+        // new column of L broadcast through LDS.
         const int mat = lane >> 5, i = lane & 31;
         if (wave == 0 && i < W2) {
             d2 *M = mat ? sG : sF;
-            d2 *lb = lbuf[mat];
+            d2 *lb = lbuf[mat][0];
             d2 a[W2];
 #pragma unroll
             for (int k = 0; k < W2; ++k) a[k] = M[k * LDI + i];
