@@ -196,17 +196,39 @@ __device__ __forceinline__ void inner_solve(
         }
         if (tid == 0) s_fail = 0;
     } else {
-        for (int e = 2 * tid; e < W2 * W2; e += 2 * NT) {
-            // upper tiles of a Gram are never read
-            if ((e / W2) / 16 > (e % W2) / 16) continue;
-            d2 a = *(const d2 *)(pa + e), b = *(const d2 *)(pb + e);
-            for (int sp = 1; sp < nsplit; ++sp) {
-                a += *(const d2 *)(pa + sp * sstride + e);
-                b += *(const d2 *)(pb + sp * sstride + e);
-            }
-            const int col = e / W2, row = e % W2;
-            *(d2 *)(sF + col * LDI + row) = a;
-            *(d2 *)(sG + col * LDI + row) = b;
+        // SB partials of every element in flight at a time
+        constexpr int NIT = (W2 * W2) / (2 * NT), SB = NIT > 16 ? 1 : 16 / NIT;
+        d2 va[NIT], vb[NIT];
+        for (int s0 = 0; s0 < nsplit; s0 += SB) {
+            d2 ta[SB][NIT], tb[SB][NIT];
+#pragma unroll
+            for (int u = 0; u < SB; ++u)
+                if (s0 + u < nsplit) {
+#pragma unroll
+                    for (int it = 0; it < NIT; ++it) {
+                        const int e = 2 * tid + 2 * NT * it;
+                        // upper tiles of a Gram are never read
+                        if ((e / W2) / 16 > (e % W2) / 16) continue;
+                        ta[u][it] = *(const d2 *)(pa + (s0 + u) * sstride + e);
+                        tb[u][it] = *(const d2 *)(pb + (s0 + u) * sstride + e);
+                    }
+                }
+#pragma unroll
+            for (int u = 0; u < SB; ++u)
+                if (s0 + u < nsplit) {
+#pragma unroll
+                    for (int it = 0; it < NIT; ++it) {
+                        va[it] = (s0 + u) ? va[it] + ta[u][it] : ta[u][it];
+                        vb[it] = (s0 + u) ? vb[it] + tb[u][it] : tb[u][it];
+                    }
+                }
+        }
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int e = 2 * tid + 2 * NT * it, col = e / W2, row = e % W2;
+            if (col / 16 > row / 16) continue;
+            *(d2 *)(sF + col * LDI + row) = va[it];
+            *(d2 *)(sG + col * LDI + row) = vb[it];
         }
         if (tid == 0) s_fail = 0;
     }

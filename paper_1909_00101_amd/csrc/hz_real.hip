@@ -59,8 +59,9 @@ __global__ __launch_bounds__(256) void k_prescale_copy(
 // the MFMA operand registers, two chunks in flight) into the lower-triangle
 // 16x16 tiles of a W2 x W2 partial Gram (the inner solver reads only the
 // lower triangle); each of the four waves takes a 16-row slab of every
-// chunk, and their partials are summed as (w0 + w1) + (w2 + w3).  k_gram_sum then adds the split partials in split order:
-// no floating-point atomics, so the result is reproducible bit for bit.
+// chunk, and their partials are summed as (w0 + w1) + (w2 + w3).  The inner
+// solver or k_gram_sum then adds the split partials in split order: no
+// floating-point atomics, so the result is reproducible bit for bit.
 // ------------------------------------------------------------------------
 template <int W2>
 __global__ __launch_bounds__(256) void k_gram(const double *__restrict__ Fw,
@@ -513,17 +514,22 @@ static void step_impl(const Plan &P, const Ptrs &W, int step, const hz_params &p
                       hipStream_t s)
 {
     const int *pairs = W.otab + (size_t)step * P.npairs * 2;
+    // The inner solver adds the row-split partials itself where they are few
+    // bytes for its one workgroup: always for 2w <= 32 (2w = 32: 8 partials cost
+    // it 0.5 us and 16 2.4 us, k_gram_sum 2.4 us and the gap before it), up to 4
+    // for 2w = 64 (1.8 us; 8 cost 4.4 us and 4096x1024 60.6 -> 61.4 ms).
+    const bool fold = !prm.pivot_qr && (W2 <= 32 || P.splits <= 4);
     prof_mark(K_GRAM, true, s);
     if (prm.pivot_qr) {
         launch_pivot_qr(P, W, step, s);
     } else {
         hipLaunchKernelGGL(k_gram<W2>, dim3(P.splits, P.npairs, 2), dim3(256), 0, s, W.Fw, W.Gw,
                            P.mfw, P.mgw, pairs, P.splits, W.part);
-        launch_gram_sum(P, W, s);
+        if (!fold) launch_gram_sum(P, W, s);
     }
     prof_mark(K_GRAM, false, s);
     prof_mark(K_INNER, true, s);
-    inner_impl<W2>(P, W, step, prm, tol, false, s);
+    inner_impl<W2>(P, W, step, prm, tol, fold, s);
     prof_mark(K_INNER, false, s);
     const int64_t rpt = 4 * (int64_t)P.upd_rows;
     const int nt = (int)((P.mfw + P.mgw + P.nzw + rpt - 1) / rpt);
