@@ -144,7 +144,49 @@ void launch_gram_sum(const Plan &P, const Ptrs &W, hipStream_t s);
 void launch_pivot_qr(const Plan &P, const Ptrs &W, int step, hipStream_t s);
 int pivot_qr_tiles(const Plan &P);   // leaf tiles of the taller matrix
 void launch_inner_real(const Plan &P, const Ptrs &W, int step, const hz_params &prm, double tol,
-                       bool partials, hipStream_t s);
+                       bool f32, hipStream_t s);
+
+// What the workgroups past the pairs of an inner launch do (k_inner_side), on
+// the compute units that the pairs leave idle: an inner solve is one workgroup.
+//  - nblk of them per pair apply the step before to the rows of Z (FP64, or
+//    FP32 with f32), `rows` rows each.  Nothing reads Z before the end of the
+//    sweep, so the update of a step leaves Z out, except the last step's;
+//    Z_tilde alternates between two buffers.
+//  - noffd of them form the off-diagonal measure of the Gram blocks (FP32
+//    phase of the mixed form).
+struct InnerSide {
+    int nblk, rows, f32, noffd;
+    void *Zw;
+    int64_t nzw;
+    const int *pairs;                  // of the step before
+    const double *Zt;
+    const unsigned long long *cnt;
+    const double *blocks;
+    int64_t bstride;                   // from a matrix's Gram block to the next
+    double *offd;
+};
+// Rows of Z per side workgroup of nw waves: four 16-row tiles per wave.
+inline int side_rows(int nw) { return 64 * nw; }
+// Whether Z goes aside.  The workgroups cost the launch 1.3 us, so Z has to be
+// large (n = 2048, 2w = 64: 8192 rows 76.9 -> 70.4 ms for 5 sweeps, 3072 rows
+// 45.5 -> 42.3; 6144x1536 41.3 -> 40.4; 4096x1024 60.0 -> 60.2 ms for 19) or a
+// large part of the rows (1100x1024 16.4 -> 15.7 ms for 5 sweeps), or other
+// work is there for them (mixed form: 198 -> 189 ms for 8192x2048); 2w = 32
+// gains nothing (1024x1024: 53.2 -> 53.5 ms for 20).  Beyond four workgroups
+// per idle compute unit (of 256) they would outlast the inner solve.
+inline bool z_aside(const Plan &P, const hz_params &prm)
+{
+    if (P.W2 != 64 || prm.pivot_qr || P.npairs >= 256) return false;
+    const int rows = side_rows(P.w * P.inner_lp / 64);
+    return (P.mixed || P.nzw >= 1536 || (P.nzw >= 1024 && 4 * P.nzw >= P.mfw + P.mgw)) &&
+           P.npairs * ((P.nzw + rows - 1) / rows) <= 4 * (256 - P.npairs);
+}
+// Z_tilde of a step: with Z aside, the odd steps' in the buffer of the pivot
+// factors, which only pivot_qr uses.
+inline double *zt_of(const Ptrs &W, int step, bool aside)
+{
+    return aside && (step & 1) ? W.gram : W.Zt;
+}
 
 // Per-sweep summary written by k_sweep_totals: sums of the per-(step, pair)
 // counters, the largest off-diagonal measure (mixed form, as bits of a

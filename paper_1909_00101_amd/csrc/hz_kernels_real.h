@@ -9,6 +9,16 @@
 
 namespace hz {
 
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+
+// v_mfma_f32_16x16x4_f32: A[i][k] lane i + 16k, B[k][j] lane j + 16k,
+// C[i][j] lane j + 16*(i/4), element i%4 (checked on gfx950).
+__device__ __forceinline__ f4 mfma16f(float a, float b, f4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 // LDS (doubles) each body needs; the caller provides it, so one kernel can
 // run several bodies over a single allocation.
 // (gram: two regions for the waves' partial blocks with stride W2 + 2,
@@ -154,7 +164,8 @@ template <int W2, int LP, int ORD, bool GEN>
 __device__ __forceinline__ void inner_solve(
     const double *__restrict__ pa, const double *__restrict__ pb, int nsplit, size_t sstride,
     int inner_max, double tol, int sort, int variant, double *__restrict__ zt,
-    unsigned long long *__restrict__ myc, int *__restrict__ status, int failcode, unsigned long long *__restrict__ ph, double *__restrict__ lds)
+    unsigned long long *__restrict__ myc, int *__restrict__ status, int failcode,
+    unsigned long long *__restrict__ ph, double *__restrict__ lds)
 {
     constexpr int NT = (W2 / 2) * LP;
     constexpr int LDI = W2 + 2;
@@ -471,6 +482,137 @@ __device__ __forceinline__ void update_rows(double *__restrict__ Y, int64_t m, i
             r = v;
         },
         p, q, rb, re, zt, sz);
+}
+
+// The same on FP32 rows (tiles of 32 rows), with Z_tilde rounded to FP32 (sz:
+// W2 * (W2 + 1) floats).
+template <int W2, int NW, class Locate>
+__device__ __forceinline__ void update32_row_seq(Locate locate, int p, int q, int64_t rb,
+                                                 int64_t re, const double *__restrict__ zt,
+                                                 float *__restrict__ sz)
+{
+    constexpr int W = W2 / 2, NB = W2 / 16, KS = W2 / 4, LDZ = W2 + 1, NTH = 64 * NW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    {
+        // every load of a thread issued before the first store
+        constexpr int NZ = (W2 * W2) / NTH;
+        static_assert(NZ * NTH == W2 * W2, "Z_tilde staging geometry");
+        double zv[NZ];
+#pragma unroll
+        for (int it = 0; it < NZ; ++it) zv[it] = zt[tid + NTH * it];
+#pragma unroll
+        for (int it = 0; it < NZ; ++it) {
+            const int e = tid + NTH * it;
+            sz[(e / W2) * LDZ + (e % W2)] = (float)zv[it];
+        }
+    }
+    __syncthreads();
+    const int k4 = lane >> 4, i16 = lane & 15;
+    for (int64_t v0 = rb + 32 * wave; v0 < re; v0 += 32 * NW) {
+        __asm__ volatile("" ::: "memory");
+        float *Y;
+        int64_t m, r0;
+        locate(v0, Y, m, r0);
+        float *bp = Y + ((int64_t)p * W + k4) * m + 2 * i16;
+        float *bq = Y + ((int64_t)q * W + k4) * m + 2 * i16;
+        f2 xb[KS];
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            xb[s] = (4 * s < W) ? *(const f2 *)(bp + (int64_t)(4 * s) * m + r0)
+                                : *(const f2 *)(bq + (int64_t)(4 * s - W) * m + r0);
+        f4 ae[NB], ao[NB];
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) {
+            ae[jb] = f4{0.f, 0.f, 0.f, 0.f};
+            ao[jb] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb) {
+                const float za = sz[(16 * jb + i16) * LDZ + 4 * s + k4];
+                ae[jb] = mfma16f(za, xb[s][0], ae[jb]);
+                ao[jb] = mfma16f(za, xb[s][1], ao[jb]);
+            }
+        // output column 16jb + 4*k4 + r, rows r0 + 2*i16 (+1): stored through
+        // the base pointers (which already carry the k4 column offset)
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int c0 = 16 * jb + 3 * k4 + r;   // + k4 via the base pointer
+                const int cabs = 16 * jb + 4 * k4 + r;
+                float *dst = (cabs < W) ? bp + (int64_t)c0 * m + r0 : bq + (int64_t)(c0 - W) * m + r0;
+                *(f2 *)dst = f2{ae[jb][r], ao[jb][r]};
+            }
+    }
+}
+
+// Off-diagonal measure of the FP32 phase (reading R20) of one Gram block A:
+// max over its off-diagonal entries of |A_ij| / sqrt(A_ii A_jj), by a
+// workgroup of NT threads; lds: W2 + NT doubles.
+template <int W2, int NT>
+__device__ __forceinline__ void offdiag_block(const double *__restrict__ A,
+                                              double *__restrict__ out, double *__restrict__ lds)
+{
+    double *const dg = lds, *const red = lds + W2;
+    const int tid = threadIdx.x;
+    for (int i = tid; i < W2; i += NT) dg[i] = A[i * W2 + i];
+    __syncthreads();
+    double mx = 0.0;
+    // every load of a thread issued before the first use (the upper
+    // entries are loaded and left unused)
+    constexpr int NIT = (W2 * W2) / NT;
+    static_assert(NIT * NT == W2 * W2, "off-diagonal geometry");
+    double av[NIT];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) av[it] = A[tid + NT * it];
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+        const int e = tid + NT * it, col = e / W2, row = e % W2;
+        if (row > col) {
+            const double v = fabs(av[it]) / sqrt(dg[row] * dg[col]);
+            mx = (v > mx) ? v : mx;
+        }
+    }
+    red[tid] = mx;
+    __syncthreads();
+    for (int h = NT / 2; h > 0; h >>= 1) {
+        if (tid < h) red[tid] = (red[tid + h] > red[tid]) ? red[tid + h] : red[tid];
+        __syncthreads();
+    }
+    if (tid == 0) *out = red[0];
+}
+
+// Side workgroup b of an inner launch (see InnerSide).
+template <int W2, int NT>
+__device__ __forceinline__ void inner_side(const InnerSide &S, int npairs, int b,
+                                           double *__restrict__ lds)
+{
+    if (b >= npairs * S.nblk) {
+        const int pm = b - npairs * S.nblk;
+        offdiag_block<W2, NT>(S.blocks + pm * S.bstride, S.offd + pm, lds);
+        return;
+    }
+    const int pr = b / S.nblk;
+    if (S.cnt[(size_t)pr * 4 + 3]) return;   // Z_tilde = I
+    const int p = S.pairs[2 * pr], q = S.pairs[2 * pr + 1];
+    const int64_t rb = (int64_t)(b - pr * S.nblk) * S.rows;
+    const int64_t re = rb + S.rows < S.nzw ? rb + S.rows : S.nzw;
+    const double *zt = S.Zt + (size_t)pr * (W2 * W2);
+    if (S.f32) {
+        float *const Z = (float *)S.Zw;
+        const int64_t m = S.nzw;
+        update32_row_seq<W2, NT / 64>(
+            [=](int64_t v, float *&y, int64_t &ld, int64_t &r) {
+                y = Z;
+                ld = m;
+                r = v;
+            },
+            p, q, rb, re, zt, (float *)lds);
+    } else {
+        update_rows<W2, NT / 64>((double *)S.Zw, S.nzw, p, q, rb, re, zt, lds);
+    }
 }
 
 }  // namespace hz

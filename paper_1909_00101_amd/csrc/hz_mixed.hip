@@ -9,18 +9,9 @@
 // (paper, Section 2.1: the transformations accumulate into Z).
 #include "hz_device.h"
 #include "hz_internal.h"
+#include "hz_kernels_real.h"
 
 namespace hz {
-
-typedef float f4 __attribute__((ext_vector_type(4)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-
-// v_mfma_f32_16x16x4_f32: A[i][k] lane i + 16k, B[k][j] lane j + 16k,
-// C[i][j] lane j + 16*(i/4), element i%4 (checked on gfx950).
-__device__ __forceinline__ f4 mfma16f(float a, float b, f4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 
 // Prescale (Section 2) into FP32 working copies, with bordering.
 __global__ __launch_bounds__(256) void k_prescale_copy32(
@@ -154,26 +145,9 @@ __global__ __launch_bounds__(256) void k_update32(float *__restrict__ Fs, float 
                                                   int rows_per_wave,
                                                   const unsigned long long *__restrict__ scnt)
 {
-    constexpr int W = W2 / 2, NB = W2 / 16, KS = W2 / 4, LDZ = W2 + 1;
-    __shared__ float sz[W2 * LDZ];
+    __shared__ float sz[W2 * (W2 + 1)];
     const int pr = blockIdx.y;
     if (scnt[(size_t)pr * 4 + 3]) return;   // Z_tilde = I: nothing to update
-    const int p = pairs[2 * pr], q = pairs[2 * pr + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double *zt = Zt + (size_t)pr * (W2 * W2);
-    {
-        // every load of a thread issued before the first store
-        constexpr int NZ = (W2 * W2) / 256;
-        static_assert(NZ * 256 == W2 * W2, "Z_tilde staging geometry");
-        double zv[NZ];
-#pragma unroll
-        for (int it = 0; it < NZ; ++it) zv[it] = zt[tid + 256 * it];
-#pragma unroll
-        for (int it = 0; it < NZ; ++it) {
-            const int e = tid + 256 * it;
-            sz[(e / W2) * LDZ + (e % W2)] = (float)zv[it];
-        }
-    }
     // The rows of F, G and Z (each a multiple of 64) are taken as one
     // sequence cut into workgroup ranges of 4 * rows_per_wave rows (a
     // multiple of 64); a 32-row tile never straddles two matrices, and its
@@ -181,98 +155,33 @@ __global__ __launch_bounds__(256) void k_update32(float *__restrict__ Fs, float 
     const int64_t span = 4 * (int64_t)rows_per_wave;
     const int64_t vb = (int64_t)blockIdx.x * span, total = mfw + mgw + nzw;
     const int64_t ve = (vb + span < total) ? vb + span : total;
-    __syncthreads();
-    const int k4 = lane >> 4, i16 = lane & 15;
-    for (int64_t v0 = vb + 32 * wave; v0 < ve; v0 += 128) {
-        __asm__ volatile("" ::: "memory");
-        float *Y;
-        int64_t m, r0;
-        if (v0 < mfw) {
-            Y = Fs;
-            m = mfw;
-            r0 = v0;
-        } else if (v0 < mfw + mgw) {
-            Y = Gs;
-            m = mgw;
-            r0 = v0 - mfw;
-        } else {
-            Y = Zs;
-            m = nzw;
-            r0 = v0 - mfw - mgw;
-        }
-        float *bp = Y + ((int64_t)p * W + k4) * m + 2 * i16;
-        float *bq = Y + ((int64_t)q * W + k4) * m + 2 * i16;
-        f2 xb[KS];
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-            xb[s] = (4 * s < W) ? *(const f2 *)(bp + (int64_t)(4 * s) * m + r0)
-                                : *(const f2 *)(bq + (int64_t)(4 * s - W) * m + r0);
-        f4 ae[NB], ao[NB];
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb) {
-            ae[jb] = f4{0.f, 0.f, 0.f, 0.f};
-            ao[jb] = f4{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) {
-                const float za = sz[(16 * jb + i16) * LDZ + 4 * s + k4];
-                ae[jb] = mfma16f(za, xb[s][0], ae[jb]);
-                ao[jb] = mfma16f(za, xb[s][1], ao[jb]);
+    update32_row_seq<W2, 4>(
+        [=](int64_t v, float *&y, int64_t &ld, int64_t &r) {
+            if (v < mfw) {
+                y = Fs;
+                ld = mfw;
+                r = v;
+            } else if (v < mfw + mgw) {
+                y = Gs;
+                ld = mgw;
+                r = v - mfw;
+            } else {
+                y = Zs;
+                ld = nzw;
+                r = v - mfw - mgw;
             }
-        // output column 16jb + 4*k4 + r, rows r0 + 2*i16 (+1): stored through
-        // the base pointers (which already carry the k4 column offset)
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int c0 = 16 * jb + 3 * k4 + r;   // + k4 via the base pointer
-                const int cabs = 16 * jb + 4 * k4 + r;
-                float *dst = (cabs < W) ? bp + (int64_t)c0 * m + r0 : bq + (int64_t)(c0 - W) * m + r0;
-                *(f2 *)dst = f2{ae[jb][r], ao[jb][r]};
-            }
-    }
+        },
+        pairs[2 * pr], pairs[2 * pr + 1], vb, ve, Zt + (size_t)pr * (W2 * W2), sz);
 }
 
-// Off-diagonal measure of the FP32 phase (reading R20): for the Gram blocks
-// of one step, max over pairs and off-diagonal entries of
-// |A_ij| / sqrt(A_ii A_jj) and |B_ij| / sqrt(B_ii B_jj).  One workgroup per
-// (pair, matrix); the result is written per (step, pair, matrix).
+// The off-diagonal measures of a step's Gram blocks (bstride apart), one
+// workgroup per (pair, matrix), where they are not done beside the inner solves.
 template <int W2>
-__global__ __launch_bounds__(256) void k_offdiag(const double *__restrict__ gram, int step,
-                                                 int npairs, double *__restrict__ offd)
+__global__ __launch_bounds__(256) void k_offdiag(const double *__restrict__ blocks,
+                                                 int64_t bstride, double *__restrict__ offd)
 {
-    __shared__ double dg[W2];
-    __shared__ double red[256];
-    const int pm = blockIdx.x;
-    const double *A = gram + (size_t)pm * (W2 * W2);
-    const int tid = threadIdx.x;
-    for (int i = tid; i < W2; i += 256) dg[i] = A[i * W2 + i];
-    __syncthreads();
-    double mx = 0.0;
-    // every load of a thread issued before the first use (the upper
-    // entries are loaded and left unused)
-    constexpr int NIT = (W2 * W2) / 256;
-    static_assert(NIT * 256 == W2 * W2, "off-diagonal geometry");
-    double av[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) av[it] = A[tid + 256 * it];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int e = tid + 256 * it, col = e / W2, row = e % W2;
-        if (row > col) {
-            const double v = fabs(av[it]) / sqrt(dg[row] * dg[col]);
-            mx = (v > mx) ? v : mx;
-        }
-    }
-    red[tid] = mx;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (tid < h) red[tid] = (red[tid + h] > red[tid]) ? red[tid + h] : red[tid];
-        __syncthreads();
-    }
-    if (tid == 0) offd[(size_t)step * npairs * 2 + pm] = red[0];
+    __shared__ double lds[W2 + 256];
+    offdiag_block<W2, 256>(blocks + blockIdx.x * bstride, offd + blockIdx.x, lds);
 }
 
 // FP64 restart GEMM C(rows, N) = A(rows, K) * B(K, N) with A FP64 (the
@@ -369,17 +278,20 @@ static void step32_impl(const Plan &P, const Ptrs &W, int step, const hz_params 
     hipLaunchKernelGGL(k_gram32<W2>, dim3(P.splits, P.npairs, 2), dim3(256), 0, s, W.Fs, W.Gs,
                        P.mfw, P.mgw, pairs, P.splits, W.part);
     launch_gram_sum(P, W, s);
-    hipLaunchKernelGGL(k_offdiag<W2>, dim3(2 * P.npairs), dim3(256), 0, s, W.gram, step,
-                       P.npairs, W.offd);
+    const bool aside = z_aside(P, prm);
+    if (!aside)
+        hipLaunchKernelGGL(k_offdiag<W2>, dim3(2 * P.npairs), dim3(256), 0, s, W.part,
+                           (int64_t)P.splits * (W2 * W2), W.offd + (size_t)step * P.npairs * 2);
     prof_mark(K_GRAM, false, s);
     prof_mark(K_INNER, true, s);
-    launch_inner_real(P, W, step, prm, tol, false, s);
+    launch_inner_real(P, W, step, prm, tol, true, s);
     prof_mark(K_INNER, false, s);
     const int64_t rpt = 4 * (int64_t)P.upd_rows;
-    const int nt = (int)((P.mfw + P.mgw + P.nzw + rpt - 1) / rpt);
+    const int64_t nzw = aside && step + 1 < P.steps ? 0 : P.nzw;
+    const int nt = (int)((P.mfw + P.mgw + nzw + rpt - 1) / rpt);
     prof_mark(K_UPDATE, true, s);
     hipLaunchKernelGGL(k_update32<W2>, dim3(nt, P.npairs), dim3(256), 0, s, W.Fs, W.Gs, W.Zs,
-                       P.mfw, P.mgw, P.nzw, pairs, W.Zt, P.upd_rows,
+                       P.mfw, P.mgw, nzw, pairs, zt_of(W, step, aside), P.upd_rows,
                        W.cnt + (size_t)step * P.npairs * 4);
     prof_mark(K_UPDATE, false, s);
 }

@@ -79,19 +79,18 @@ __global__ __launch_bounds__(256) void k_gram(const double *__restrict__ Fw,
 }
 
 // Sum of the Gram split partials in split order (fixed association, so the
-// result is reproducible bit for bit): grid (W2*W2/512, 2 * pairs), 256
-// threads, two consecutive elements per thread, every split's load issued
-// before the adds.
+// result is reproducible bit for bit), in place of the first: grid (W2*W2/512,
+// 2 * pairs), 256 threads, two consecutive elements per thread, every split's
+// load issued before the adds.
 template <int W2>
-__global__ __launch_bounds__(256) void k_gram_sum(const double *__restrict__ part, int splits,
-                                                  double *__restrict__ gram)
+__global__ __launch_bounds__(256) void k_gram_sum(double *__restrict__ part, int splits)
 {
     constexpr int MAXS = 16;
     const int pm = blockIdx.y;
     const int e = 2 * (blockIdx.x * 256 + threadIdx.x);
     if (e >= W2 * W2) return;
     if ((e % W2) / 16 < (e / W2) / 16) return;   // upper tiles: never read
-    const double *src = part + (size_t)pm * splits * (W2 * W2) + e;
+    double *src = part + (size_t)pm * splits * (W2 * W2) + e;
     d2 v[MAXS];
 #pragma unroll
     for (int s = 0; s < MAXS; ++s)
@@ -100,7 +99,7 @@ __global__ __launch_bounds__(256) void k_gram_sum(const double *__restrict__ par
 #pragma unroll
     for (int s = 1; s < MAXS; ++s)
         if (s < splits) acc += v[s];
-    *(d2 *)(gram + (size_t)pm * (W2 * W2) + e) = acc;
+    *(d2 *)src = acc;
 }
 
 // ------------------------------------------------------------------------
@@ -126,18 +125,18 @@ __global__ __launch_bounds__(256) void k_gram_sum(const double *__restrict__ par
 //  5. Z_tilde = Z_hat Theta, Theta_jj = (||f_hat_j||^2+||g_hat_j||^2)^-1/2.
 // Counters per (step, pair): transformations, big ones, inner sweeps run.
 // ------------------------------------------------------------------------
+// blocks: per pair the two matrices' blocks, bstride apart.
 template <int W2, int LP, int ORD, bool GEN>
-__device__ __forceinline__ void inner_body(const double *gram, int nsplit, int npairs, int step,
-                                           int inner_max, double tol, int sort, int variant,
-                                           double *Zt, unsigned long long *cnt, int *status,
-                                           unsigned long long *phase)
+__device__ __forceinline__ void inner_body(const double *blocks, int64_t bstride, int nsplit,
+                                           int npairs, int step, int inner_max, double tol,
+                                           int sort, int variant, double *Zt,
+                                           unsigned long long *cnt, int *status,
+                                           unsigned long long *phase, double *lds)
 {
     const int pr = blockIdx.x;
-    const int ns = nsplit > 0 ? nsplit : 1;   // nsplit 0: one triangular factor per matrix
-    const double *pa = gram + (size_t)(pr * 2) * ns * (W2 * W2);
-    __shared__ __attribute__((aligned(16))) double lds[inner_lds<W2>()];
-    inner_solve<W2, LP, ORD, GEN>(pa, pa + (size_t)ns * (W2 * W2), nsplit, W2 * W2, inner_max, tol,
-                                  sort, variant, Zt + (size_t)pr * (W2 * W2),
+    const double *pa = blocks + 2 * pr * bstride;
+    inner_solve<W2, LP, ORD, GEN>(pa, pa + bstride, nsplit, W2 * W2, inner_max, tol, sort, variant,
+                                  Zt + (size_t)pr * (W2 * W2),
                                   cnt + ((size_t)step * npairs + pr) * 4, status,
                                   step * 65536 + pr,
                                   phase ? phase + ((size_t)step * npairs + pr) * 8 : nullptr, lds);
@@ -146,25 +145,45 @@ __device__ __forceinline__ void inner_body(const double *gram, int nsplit, int n
 // variant 0 with sorting, the default
 template <int W2, int LP, int ORD>
 __global__ __launch_bounds__((W2 / 2) * LP) void k_inner(
-    const double *__restrict__ gram, int nsplit, int npairs, int step, int inner_max, double tol,
-    int sort, int variant, double *__restrict__ Zt,
+    const double *__restrict__ blocks, int64_t bstride, int nsplit, int npairs, int step,
+    int inner_max, double tol, int sort, int variant, double *__restrict__ Zt,
     unsigned long long *__restrict__ cnt, int *__restrict__ status,
     unsigned long long *__restrict__ phase)
 {
-    inner_body<W2, LP, ORD, false>(gram, nsplit, npairs, step, inner_max, tol, sort, variant,
-                                   Zt, cnt, status, phase);
+    __shared__ __attribute__((aligned(16))) double lds[inner_lds<W2>()];
+    inner_body<W2, LP, ORD, false>(blocks, bstride, nsplit, npairs, step, inner_max, tol, sort,
+                                   variant, Zt, cnt, status, phase, lds);
 }
 
 // any variant, sorted or not
 template <int W2, int LP, int ORD>
 __global__ __launch_bounds__((W2 / 2) * LP) void k_inner_any(
-    const double *__restrict__ gram, int nsplit, int npairs, int step, int inner_max, double tol,
-    int sort, int variant, double *__restrict__ Zt,
+    const double *__restrict__ blocks, int64_t bstride, int nsplit, int npairs, int step,
+    int inner_max, double tol, int sort, int variant, double *__restrict__ Zt,
     unsigned long long *__restrict__ cnt, int *__restrict__ status,
     unsigned long long *__restrict__ phase)
 {
-    inner_body<W2, LP, ORD, true>(gram, nsplit, npairs, step, inner_max, tol, sort, variant,
-                                  Zt, cnt, status, phase);
+    __shared__ __attribute__((aligned(16))) double lds[inner_lds<W2>()];
+    inner_body<W2, LP, ORD, true>(blocks, bstride, nsplit, npairs, step, inner_max, tol, sort,
+                                  variant, Zt, cnt, status, phase, lds);
+}
+
+// 2w = 64, with side workgroups (see InnerSide).  A kernel of its own: their
+// arguments and registers cost the plain launch 0.6 us.
+template <int LP, int ORD, bool GEN>
+__global__ __launch_bounds__(32 * LP) void k_inner_side(
+    const double *__restrict__ blocks, int64_t bstride, int nsplit, int npairs, int step,
+    int inner_max, double tol, int sort, int variant, double *__restrict__ Zt,
+    unsigned long long *__restrict__ cnt, int *__restrict__ status,
+    unsigned long long *__restrict__ phase, InnerSide side)
+{
+    __shared__ __attribute__((aligned(16))) double lds[inner_lds<64>()];
+    if ((int)blockIdx.x >= npairs) {
+        inner_side<64, 32 * LP>(side, npairs, blockIdx.x - npairs, lds);
+        return;
+    }
+    inner_body<64, LP, ORD, GEN>(blocks, bstride, nsplit, npairs, step, inner_max, tol, sort,
+                                 variant, Zt, cnt, status, phase, lds);
 }
 
 // ------------------------------------------------------------------------
@@ -448,63 +467,103 @@ void launch_prescale_real(const Plan &P, const Ptrs &W, const double *F, int64_t
                        ldg, P.nw, P.mfw, P.mgw, P.nzw, W.Fw, W.Gw, W.Zw, W.status);
 }
 
+// Whether the inner solver adds the Gram's row-split partials itself: where
+// they are few bytes for its one workgroup, always for 2w <= 32 (2w = 32: 8
+// partials cost it 0.5 us and 16 2.4 us, k_gram_sum 2.4 us and the gap before
+// it), up to 4 for 2w = 64 (1.8 us; 8 cost 4.4 us and 4096x1024 60.6 -> 61.4
+// ms).  The off-diagonal measure of the FP32 phase takes the sums.
+static bool inner_sums(const Plan &P, bool f32) { return !f32 && (P.W2 <= 32 || P.splits <= 4); }
+
 template <int W2, int LP>
 static void inner_launch(const Plan &P, const Ptrs &W, int step, const hz_params &prm,
-                         double tol, const double *src, int ns, hipStream_t s)
+                         double tol, bool f32, hipStream_t s)
 {
+    constexpr int NT = (W2 / 2) * LP;
+    const double *blocks = prm.pivot_qr ? W.gram : W.part;
+    const int64_t bstride = (int64_t)(W2 * W2) * (prm.pivot_qr ? 1 : P.splits);
+    const int ns = prm.pivot_qr ? 0 : inner_sums(P, f32) ? P.splits : 1;
+    const bool def = prm.variant == 0 && prm.sort;
+    const bool aside = z_aside(P, prm);
+    double *const zt = zt_of(W, step, aside);
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(P.npairs), dim3((W2 / 2) * LP), 0, s, src, ns, P.npairs, step,
-                           prm.inner_max_sweeps, tol, prm.sort, prm.variant, W.Zt, W.cnt,
+        hipLaunchKernelGGL(kern, dim3(P.npairs), dim3(NT), 0, s, blocks, bstride, ns, P.npairs,
+                           step, prm.inner_max_sweeps, tol, prm.sort, prm.variant, zt, W.cnt,
                            W.status, W.phase);
     };
-    const bool std = prm.variant == 0 && prm.sort;
+    auto pick = [&](auto ord_c) {
+        constexpr int ORD = decltype(ord_c)::value;
+        if constexpr (W2 == 64) {
+            if (aside) {
+                InnerSide side = {};
+                side.rows = side_rows(NT / 64);
+                side.f32 = f32;
+                side.Zw = f32 ? (void *)W.Zs : (void *)W.Zw;
+                side.nzw = P.nzw;
+                if (step > 0) {
+                    side.nblk = (int)((P.nzw + side.rows - 1) / side.rows);
+                    side.pairs = W.otab + (size_t)(step - 1) * P.npairs * 2;
+                    side.Zt = zt_of(W, step - 1, true);
+                    side.cnt = W.cnt + (size_t)(step - 1) * P.npairs * 4;
+                }
+                if (f32) {
+                    side.noffd = 2 * P.npairs;
+                    side.blocks = blocks;
+                    side.bstride = bstride;
+                    side.offd = W.offd + (size_t)step * P.npairs * 2;
+                }
+                auto go_side = [&](auto kern) {
+                    hipLaunchKernelGGL(kern, dim3(P.npairs * (1 + side.nblk) + side.noffd),
+                                       dim3(NT), 0, s, blocks, bstride, ns, P.npairs, step,
+                                       prm.inner_max_sweeps, tol, prm.sort, prm.variant, zt,
+                                       W.cnt, W.status, W.phase, side);
+                };
+                def ? go_side(k_inner_side<LP, ORD, false>) : go_side(k_inner_side<LP, ORD, true>);
+                return;
+            }
+        }
+        def ? go(k_inner<W2, LP, ORD>) : go(k_inner_any<W2, LP, ORD>);
+    };
     switch (prm.inner_ordering) {
-    case HZ_ORD_MM: std ? go(k_inner<W2, LP, HZ_ORD_MM>) : go(k_inner_any<W2, LP, HZ_ORD_MM>); break;
-    case HZ_ORD_RR: std ? go(k_inner<W2, LP, HZ_ORD_RR>) : go(k_inner_any<W2, LP, HZ_ORD_RR>); break;
-    default: std ? go(k_inner<W2, LP, HZ_ORD_RING>) : go(k_inner_any<W2, LP, HZ_ORD_RING>); break;
+    case HZ_ORD_MM: pick(std::integral_constant<int, HZ_ORD_MM>()); break;
+    case HZ_ORD_RR: pick(std::integral_constant<int, HZ_ORD_RR>()); break;
+    default: pick(std::integral_constant<int, HZ_ORD_RING>()); break;
     }
 }
 
 template <int W2>
 static void inner_impl(const Plan &P, const Ptrs &W, int step, const hz_params &prm, double tol,
-                       bool partials, hipStream_t s)
+                       bool f32, hipStream_t s)
 {
-    const double *src = partials ? W.part : W.gram;
-    const int ns = partials ? P.splits : (prm.pivot_qr ? 0 : 1);
     if constexpr (W2 == 16) {
-        inner_launch<W2, 8>(P, W, step, prm, tol, src, ns, s);
+        inner_launch<W2, 8>(P, W, step, prm, tol, f32, s);
     } else {
-        if (P.inner_lp == 4) inner_launch<W2, 4>(P, W, step, prm, tol, src, ns, s);
-        else if (P.inner_lp == 8) inner_launch<W2, 8>(P, W, step, prm, tol, src, ns, s);
-        else inner_launch<W2, 16>(P, W, step, prm, tol, src, ns, s);
+        if (P.inner_lp == 4) inner_launch<W2, 4>(P, W, step, prm, tol, f32, s);
+        else if (P.inner_lp == 8) inner_launch<W2, 8>(P, W, step, prm, tol, f32, s);
+        else inner_launch<W2, 16>(P, W, step, prm, tol, f32, s);
     }
 }
 
 void launch_inner_real(const Plan &P, const Ptrs &W, int step, const hz_params &prm, double tol,
-                       bool partials, hipStream_t s)
+                       bool f32, hipStream_t s)
 {
     switch (P.W2) {
-    case 16: inner_impl<16>(P, W, step, prm, tol, partials, s); break;
-    case 32: inner_impl<32>(P, W, step, prm, tol, partials, s); break;
-    default: inner_impl<64>(P, W, step, prm, tol, partials, s); break;
+    case 16: inner_impl<16>(P, W, step, prm, tol, f32, s); break;
+    case 32: inner_impl<32>(P, W, step, prm, tol, f32, s); break;
+    default: inner_impl<64>(P, W, step, prm, tol, f32, s); break;
     }
 }
 
 void launch_gram_sum(const Plan &P, const Ptrs &W, hipStream_t s)
 {
-    const int W2 = P.W2;
-    switch (W2) {
+    switch (P.W2) {
     case 16:
-        hipLaunchKernelGGL(k_gram_sum<16>, dim3(1, 2 * P.npairs), dim3(256), 0, s, W.part,
-                           P.splits, W.gram);
+        hipLaunchKernelGGL(k_gram_sum<16>, dim3(1, 2 * P.npairs), dim3(256), 0, s, W.part, P.splits);
         break;
     case 32:
-        hipLaunchKernelGGL(k_gram_sum<32>, dim3(2, 2 * P.npairs), dim3(256), 0, s, W.part,
-                           P.splits, W.gram);
+        hipLaunchKernelGGL(k_gram_sum<32>, dim3(2, 2 * P.npairs), dim3(256), 0, s, W.part, P.splits);
         break;
     default:
-        hipLaunchKernelGGL(k_gram_sum<64>, dim3(8, 2 * P.npairs), dim3(256), 0, s, W.part,
-                           P.splits, W.gram);
+        hipLaunchKernelGGL(k_gram_sum<64>, dim3(8, 2 * P.npairs), dim3(256), 0, s, W.part, P.splits);
         break;
     }
 }
@@ -514,28 +573,25 @@ static void step_impl(const Plan &P, const Ptrs &W, int step, const hz_params &p
                       hipStream_t s)
 {
     const int *pairs = W.otab + (size_t)step * P.npairs * 2;
-    // The inner solver adds the row-split partials itself where they are few
-    // bytes for its one workgroup: always for 2w <= 32 (2w = 32: 8 partials cost
-    // it 0.5 us and 16 2.4 us, k_gram_sum 2.4 us and the gap before it), up to 4
-    // for 2w = 64 (1.8 us; 8 cost 4.4 us and 4096x1024 60.6 -> 61.4 ms).
-    const bool fold = !prm.pivot_qr && (W2 <= 32 || P.splits <= 4);
     prof_mark(K_GRAM, true, s);
     if (prm.pivot_qr) {
         launch_pivot_qr(P, W, step, s);
     } else {
         hipLaunchKernelGGL(k_gram<W2>, dim3(P.splits, P.npairs, 2), dim3(256), 0, s, W.Fw, W.Gw,
                            P.mfw, P.mgw, pairs, P.splits, W.part);
-        if (!fold) launch_gram_sum(P, W, s);
+        if (!inner_sums(P, false)) launch_gram_sum(P, W, s);
     }
     prof_mark(K_GRAM, false, s);
     prof_mark(K_INNER, true, s);
-    inner_impl<W2>(P, W, step, prm, tol, fold, s);
+    inner_impl<W2>(P, W, step, prm, tol, false, s);
     prof_mark(K_INNER, false, s);
+    const bool aside = z_aside(P, prm);
+    const int64_t nzw = aside && step + 1 < P.steps ? 0 : P.nzw;
     const int64_t rpt = 4 * (int64_t)P.upd_rows;
-    const int nt = (int)((P.mfw + P.mgw + P.nzw + rpt - 1) / rpt);
+    const int nt = (int)((P.mfw + P.mgw + nzw + rpt - 1) / rpt);
     prof_mark(K_UPDATE, true, s);
     hipLaunchKernelGGL(k_update<W2>, dim3(nt, P.npairs), dim3(256), 0, s, W.Fw, W.Gw, W.Zw,
-                       P.mfw, P.mgw, P.nzw, pairs, W.Zt, P.upd_rows,
+                       P.mfw, P.mgw, nzw, pairs, zt_of(W, step, aside), P.upd_rows,
                        W.cnt + (size_t)step * P.npairs * 4);
     prof_mark(K_UPDATE, false, s);
 }
