@@ -383,7 +383,7 @@ __global__ __launch_bounds__((W2 / 2) * LP) void k_inner_z(
         return;
     }
 
-    pointwise_solve<CplxCols, W2, LP, ORD, GEN>((double *)sF, (double *)sG, (double *)sZ, s_cnt,
+    pointwise_solve<CplxCols, W2, LP, ORD, GEN, false>((double *)sF, (double *)sG, (double *)sZ, s_cnt,
                                                 inner_max, tol, sort, variant,
                                                 (double *)(Zt + (size_t)pr * (W2 * W2)), myc, ph);
 }

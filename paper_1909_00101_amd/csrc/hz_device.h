@@ -1,6 +1,7 @@
 // hz_device.h -- device-side primitives shared by the real and complex
 // kernels of the blocked implicit Hari-Zimmermann GSVD (gfx950, wave64).
 #pragma once
+#include <type_traits>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -137,6 +138,58 @@ __device__ __forceinline__ double readlane_d(double v, int l)
     const int lo = __builtin_amdgcn_readlane((int)b, l);
     const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+
+// p[i] += r(lane T + i of the lane's 16-lane row) * m, i < N: the broadcast is
+// part of the multiply-add (row_newbcast, the one move that FP64 instructions
+// take), one instruction where readlane needs two and a product.  The first
+// one waits for r to be written (two cycles).
+template <int T, int N>
+__device__ __forceinline__ void fmac_row(double *p, double r, double m)
+{
+#define HZ_FR(K, R, M, I) "\n\tv_fmac_f64_dpp %" #K ", %" #R ", %" #M " row_newbcast:%" #I " row_mask:0xf bank_mask:0xf"
+    if constexpr (N >= 8) {
+        asm("s_nop 1" HZ_FR(0, 8, 9, 10) HZ_FR(1, 8, 9, 11) HZ_FR(2, 8, 9, 12) HZ_FR(3, 8, 9, 13)
+            HZ_FR(4, 8, 9, 14) HZ_FR(5, 8, 9, 15) HZ_FR(6, 8, 9, 16) HZ_FR(7, 8, 9, 17)
+            : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]), "+v"(p[4]), "+v"(p[5]), "+v"(p[6]),
+              "+v"(p[7])
+            : "v"(r), "v"(m), "n"(T), "n"(T + 1), "n"(T + 2), "n"(T + 3), "n"(T + 4), "n"(T + 5),
+              "n"(T + 6), "n"(T + 7));
+        fmac_row<T + 8, N - 8>(p + 8, r, m);
+    } else if constexpr (N >= 4) {
+        asm("s_nop 1" HZ_FR(0, 4, 5, 6) HZ_FR(1, 4, 5, 7) HZ_FR(2, 4, 5, 8) HZ_FR(3, 4, 5, 9)
+            : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3])
+            : "v"(r), "v"(m), "n"(T), "n"(T + 1), "n"(T + 2), "n"(T + 3));
+        fmac_row<T + 4, N - 4>(p + 4, r, m);
+    } else if constexpr (N >= 2) {
+        asm("s_nop 1" HZ_FR(0, 2, 3, 4) HZ_FR(1, 2, 3, 5)
+            : "+v"(p[0]), "+v"(p[1])
+            : "v"(r), "v"(m), "n"(T), "n"(T + 1));
+        fmac_row<T + 2, N - 2>(p + 2, r, m);
+    } else if constexpr (N == 1) {
+        asm("s_nop 1" HZ_FR(0, 1, 2, 3) : "+v"(p[0]) : "v"(r), "v"(m), "n"(T));
+    }
+#undef HZ_FR
+}
+
+// Lane T's value of each 16-lane row to the row.
+template <int T>
+__device__ __forceinline__ double bcast_row(double v)
+{
+    double r;
+    asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
+        : "=v"(r) : "v"(v), "n"(T));
+    return r;
+}
+
+// f(integral_constant 0) ... f(integral_constant N - 1)
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<N, I + 1>(f);
+    }
 }
 
 // Reciprocal square root from the hardware estimate y0 = v_rsq_f64(x)

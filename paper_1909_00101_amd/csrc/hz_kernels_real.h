@@ -170,6 +170,8 @@ __device__ __forceinline__ void inner_solve(
     constexpr int NT = (W2 / 2) * LP;
     constexpr int LDI = W2 + 2;
     static_assert(NT >= 64, "bad inner geometry");
+    // With the ring the factors stay lower, L = F_hat^T.
+    constexpr bool LOWER = W2 >= 32 && NT >= 128 && ORD == HZ_ORD_RING;
     double *const sF = lds;
     double *const sG = lds + W2 * LDI;
     double *const sZ = lds + 2 * W2 * LDI;
@@ -183,7 +185,7 @@ __device__ __forceinline__ void inner_solve(
     // 1. load the Gram blocks (lower triangles) into LDS; with nsplit > 1 the
     // blocks arrive as nsplit row-split partials (stride sstride), added in
     // split order; with nsplit 0 they are the upper triangular factors
-    // themselves (QR of the block-column pairs).
+    // themselves (QR of the block-column pairs), taken in as L with LOWER.
     if (nsplit <= 1) {
         // one summed block (or a factor): every load of a thread issued
         // before the first store, so the phase costs one memory latency
@@ -202,8 +204,15 @@ __device__ __forceinline__ void inner_solve(
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int e = 2 * tid + 2 * NT * it, col = e / W2, row = e % W2;
-            *(d2 *)(sF + col * LDI + row) = va[it];
-            *(d2 *)(sG + col * LDI + row) = vb[it];
+            if (LOWER && nsplit == 0) {
+                sF[row * LDI + col] = va[it][0];
+                sF[(row + 1) * LDI + col] = va[it][1];
+                sG[row * LDI + col] = vb[it][0];
+                sG[(row + 1) * LDI + col] = vb[it][1];
+            } else {
+                *(d2 *)(sF + col * LDI + row) = va[it];
+                *(d2 *)(sG + col * LDI + row) = vb[it];
+            }
         }
         if (tid == 0) s_fail = 0;
     } else {
@@ -254,6 +263,120 @@ __device__ __forceinline__ void inner_solve(
             const double df = sF[tid * LDI + tid], dg = sG[tid * LDI + tid];
             if (!(fabs(df) > 0.0 && fabs(df) < INFINITY && fabs(dg) > 0.0 && fabs(dg) < INFINITY))
                 s_fail = 1;
+        }
+    } else if constexpr (LOWER) {
+        // Blocked right-looking Cholesky in panels of 16 columns, one wave per
+        // matrix for a panel (lane = row, in registers).  A column's entries reach
+        // the others by products with a row broadcast; as that stays within 16
+        // lanes, the diagonal block's rows are kept in every 16-lane row (q)
+        // beside the panel's (pv), and pivots and reciprocal roots are formed
+        // there: no scalar on the chain.  Entries above the diagonal are left as
+        // they come; nothing reads them.  The trailing lower tiles take A22 -= L21
+        // L21^T as FP64 MFMA products (tile (ti, tj): A operand L rows of ti, B
+        // operand L rows of tj, four k-steps of 4 panel columns), at 2w = 64 by all
+        // waves, half of them per matrix.  Bound: the instructions of the one wave,
+        // 170 cycles a column, and the latency of LDS around the tiles.  Against
+        // the form below (readlane, pivots kept by selects, two waves, and its
+        // transposition, which the prescale makes up for by reading across): 2w =
+        // 64 10.0 -> 8.3 us, 2w = 32 4.3 -> 3.5, 4096x1024 59.8 -> 58.4 ms.  The
+        // other orderings keep that one: behind this one the compiler made their
+        // sweeps 1 % slower (2w = 64, many sweeps: 291 -> 295 us).
+        constexpr int NBK = W2 / 16;
+        constexpr int WPM = W2 == 64 ? NT / 128 : 1;     // waves per matrix for the tiles
+        const int uwave = __builtin_amdgcn_readfirstlane(wave);
+        double *const M = (uwave & 1) ? sG : sF;
+        // lane j: column j's diagonal before the factorization
+        const double d0 = (lane < W2) ? M[lane * LDI + lane] : 0.0;
+        static_for<NBK>([&](auto kb_c) {
+            constexpr int kb = decltype(kb_c)::value, c0 = 16 * kb;
+            if (uwave < 2) {
+                const int row = c0 + lane;
+                const bool live = row < W2;
+                double pv[16];
+#pragma unroll
+                for (int t = 0; t < 16; ++t) pv[t] = live ? M[(c0 + t) * LDI + row] : 0.0;
+                // the diagonal block's rows, in every 16-lane row (the last
+                // panel has no others)
+                constexpr bool REP = kb + 1 < NBK;
+                double q[16];
+#pragma unroll
+                for (int t = 0; t < 16; ++t) q[t] = REP ? M[(c0 + t) * LDI + c0 + (lane & 15)] : pv[t];
+                double inv = rsqrt_nr(bcast_row<0>(q[0]));
+                static_for<16>([&](auto j_c) {
+                    constexpr int j = decltype(j_c)::value;
+                    const double lq = q[j] * inv, mq = q[j] * -inv, lp = pv[j] * inv, mp = pv[j] * -inv;
+                    pv[j] = REP ? lp : lq;
+                    if constexpr (j < 15) {
+                        // the chain: the next pivot and its reciprocal root
+                        fmac_row<j + 1, 1>(q + j + 1, lq, mq);
+                        const double piv = bcast_row<j + 1>(q[j + 1]);
+                        const double y = __builtin_amdgcn_rsq(piv);
+                        __builtin_amdgcn_sched_barrier(0);
+                        fmac_row<j + 2, 14 - j>(q + j + 2, lq, mq);
+                        if (REP) fmac_row<j + 1, 15 - j>(pv + j + 1, lq, mp);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const double e = fma(-piv * y, y, 1.0);
+                        inv = fma(y * e, fma(0.375, e, 0.5), y);
+                    }
+                });
+                if (live) {
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) M[(c0 + t) * LDI + row] = pv[t];
+                }
+            }
+            if constexpr (kb + 1 < NBK) {
+                if (WPM > 1) __syncthreads();
+                else wave_fence();
+                const int i16 = lane & 15, k4 = lane >> 4;
+                if (WPM > 1 || uwave < 2) {
+                    // a wave's tiles together: every operand loaded first, the
+                    // products of the tiles in turn (element r of lane l: row
+                    // 16 ti + 4 r + l/16, column 16 tj + l%16)
+                    constexpr int NTR = NBK - 1 - kb, TILES = NTR * (NTR + 1) / 2;
+                    constexpr int TW = (TILES + WPM - 1) / WPM;
+                    double *ct[TW];
+                    d4 acc[TW];
+                    double la[TW][4], lb[TW][4];
+#pragma unroll
+                    for (int u = 0; u < TW; ++u) {
+                        // tile n of the lower triangle, row by row (beyond the last: the last)
+                        int n = u * WPM + (WPM > 1 ? uwave >> 1 : 0), ti = 0;
+                        n = n < TILES ? n : TILES - 1;
+#pragma unroll
+                        for (int k = 1; k < NTR; ++k) ti += n >= k * (k + 1) / 2;
+                        const int tj = n - ti * (ti + 1) / 2;
+                        ct[u] = M + (16 * (kb + 1 + tj) + i16) * LDI + 16 * (kb + 1 + ti) + k4;
+                        acc[u] = d4{ct[u][0], ct[u][4], ct[u][8], ct[u][12]};
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) {
+                            const double *const lc = M + (c0 + 4 * s + k4) * LDI + 16 * (kb + 1) + i16;
+                            la[u][s] = -lc[16 * ti];
+                            lb[u][s] = lc[16 * tj];
+                        }
+                    }
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+#pragma unroll
+                        for (int u = 0; u < TW; ++u) acc[u] = mfma16(la[u][s], lb[u][s], acc[u]);
+#pragma unroll
+                    for (int u = 0; u < TW; ++u)
+                        if (u * WPM + (WPM > 1 ? uwave >> 1 : 0) < TILES) {
+                            ct[u][0] = acc[u][0];
+                            ct[u][4] = acc[u][1];
+                            ct[u][8] = acc[u][2];
+                            ct[u][12] = acc[u][3];
+                        }
+                }
+                if (WPM > 1) __syncthreads();
+                else wave_fence();
+            }
+        });
+        if (uwave < 2) {
+            // the pivots, from the roots on the diagonal of L (the pivot of a
+            // column that is not positive leaves a NaN there)
+            wave_fence();
+            const double r = (lane < W2) ? M[lane * LDI + lane] : 1.0;
+            if (!(r * r > PIV_REL<W2>() * d0 && r < INFINITY)) s_fail = 1;
         }
     } else if constexpr (W2 >= 32 && NT >= 128) {
         // Blocked right-looking Cholesky, one wave per matrix, panels of 16
@@ -393,7 +516,8 @@ __device__ __forceinline__ void inner_solve(
         return;
     }
 
-    pointwise_solve<RealCols, W2, LP, ORD, GEN>(sF, sG, sZ, s_cnt, inner_max, tol, sort, variant, zt, myc, ph);
+    pointwise_solve<RealCols, W2, LP, ORD, GEN, LOWER>(sF, sG, sZ, s_cnt, inner_max, tol, sort,
+                                                       variant, zt, myc, ph);
 #undef s_fail
 }
 

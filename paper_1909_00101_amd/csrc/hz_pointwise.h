@@ -184,6 +184,12 @@ struct RealCols {
     {
         return (2 * p + e == c) ? 1.0 : 0.0;
     }
+    // slot p of column c of L^T, L lower in M (ld ldc)
+    static __device__ __forceinline__ d2 of_lower(const double *M, int ldc, int p, int c)
+    {
+        const double a = M[2 * p * ldc + c], b = M[(2 * p + 1) * ldc + c];
+        return d2{2 * p <= c ? a : 0.0, 2 * p + 1 <= c ? b : 0.0};
+    }
 
     // One pointwise step on the group's pair (Section 2.1): the relative
     // orthogonality test, the 2x2 transformation, its classification (big
@@ -302,8 +308,8 @@ struct CplxCols {
 };
 
 // Phases 3 to 5 of the inner solver, with the columns in registers: F_hat,
-// G_hat come as triangles in sF, sG (column-major); sF, sG, sZ (ld LDI) are
-// overwritten.  A wave holds GW = 64 / LP lane groups laid side by side in
+// G_hat come as triangles in sF, sG (column-major), or with LOWER as their
+// transposes L; sF, sG, sZ (ld LDI) are overwritten.  A wave holds GW = 64 / LP lane groups laid side by side in
 // each of its four 16-lane rows (the LP lanes of a group are strided by GW);
 // a group holds a pair of columns, x for as long as the ordering lets it and
 // y for one step.  GEN: any variant, with or without sorting; else variant
@@ -346,7 +352,7 @@ struct CplxCols {
 // eighth of the inner sweeps of full-block solves (2048 x 630 94.2 -> 87.8 ms,
 // the same errors against 64-bit references, also for sigma over twelve
 // orders of magnitude).
-template <class E, int W2, int LP, int ORD, bool GEN>
+template <class E, int W2, int LP, int ORD, bool GEN, bool LOWER>
 __device__ __forceinline__ void pointwise_solve(double *__restrict__ sF, double *__restrict__ sG,
                                                 double *__restrict__ sZ,
                                                 unsigned *__restrict__ s_cnt, int inner_max,
@@ -408,10 +414,28 @@ __device__ __forceinline__ void pointwise_solve(double *__restrict__ sF, double 
     }
 
     // 3. prescale by 1/||g_c||
-    load(sF, cx, C.fx);
-    load(sG, cx, C.gx);
-    load(sF, cy, C.fy);
-    load(sG, cy, C.gy);
+    if constexpr (LOWER) {
+        // across the rows of L: 0.4 us for all waves (2w = 64) where the
+        // transposition by the two factoring waves took 1.1
+        auto read = [&](const double *M, int c, double (&v)[ND]) {
+#pragma unroll
+            for (int k = 0; k < NS; ++k) {
+                const d2 p = E::of_lower(M, LDC, slot(k), c);
+                v[2 * k] = p[0];
+                v[2 * k + 1] = p[1];
+            }
+        };
+        read(sF, cx, C.fx);
+        read(sG, cx, C.gx);
+        read(sF, cy, C.fy);
+        read(sG, cy, C.gy);
+        __syncthreads();                 // rows of columns that others store to
+    } else {
+        load(sF, cx, C.fx);
+        load(sG, cx, C.gx);
+        load(sF, cy, C.fy);
+        load(sG, cy, C.gy);
+    }
     {
         double a = 0.0, b = 0.0;
 #pragma unroll
