@@ -171,6 +171,7 @@ def cpu_baseline(F, G, tol):
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "gsvd_real_4096x1024_w32_bo_traffic.txt")
 KERNEL_SOURCES = ["paper_1909_00101_amd/csrc/hz_real.hip", "paper_1909_00101_amd/csrc/hz_kernels_real.h",
+                  "paper_1909_00101_amd/csrc/hz_pointwise.h",
                   "paper_1909_00101_amd/csrc/hz_device.h"]
 
 
@@ -720,10 +721,11 @@ def main():
             roof = dict(bound="mfma", achieved=round(achieved, 2), peak=FP64_MFMA_PEAK_TFS,
                         unit="TFLOP/s", frac=round(achieved / FP64_MFMA_PEAK_TFS, 4),
                         traffic=None)
-    lp = kw.get("inner_lanes") or (16 if w == 32 else 8)
-    ring = "true" if kw.get("inner_ordering") == hz.HZ_ORD_RING else "false"
+    iord = kw.get("inner_ordering") or hz.HZ_ORD_RR
+    lp = 8 if w == 8 or (w == 32 and iord == hz.HZ_ORD_RING) else 16
+    lp = lp if w == 8 else kw.get("inner_lanes") or lp
     names = {"gram": [f"hz::k_gram<{2 * w}>", f"hz::k_gram_sum<{2 * w}>"],
-             "inner": [f"hz::k_inner<{2 * w},{lp},{ring}>"],
+             "inner": [f"hz::k_inner<{2 * w},{lp},{iord}>"],
              "update": [f"hz::k_update<{2 * w}>"]}
     traffic = measured_traffic()
     tr = {k: (sum(traffic[n] for n in v) if all(n in traffic for n in v) else None)

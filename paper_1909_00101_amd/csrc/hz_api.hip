@@ -104,13 +104,6 @@ static int w_ok_for(const hz_params &p, int is_complex)
     return !is_complex || p.w == 0 || p.w == 8 || p.w == 16;
 }
 
-// The table the inner solver reads for a table ordering (the ring ordering
-// is generated inside the solver; a round-robin table fills its slot).
-static int inner_table_kind(int inner_ordering)
-{
-    return inner_ordering == HZ_ORD_RING ? HZ_ORD_RR : inner_ordering;
-}
-
 // Lanes per column pair in the inner solver.  One inner sweep of 16 pivot
 // pairs on which every pair rotates, 8 against 16 lanes: 2w = 32 22.4 against
 // 18.6 us in round robin and 17.0 against 14.2 in the ring ordering (a step is
@@ -148,7 +141,6 @@ static bool make_plan(const hz_params &prm, int64_t mf, int64_t mg, int64_t n, i
     P.nblk = (int)(P.nw / P.w);
     P.npairs = P.nblk / 2;
     P.steps = (prm.ordering == HZ_ORD_MM) ? P.nblk : P.nblk - 1;
-    P.isteps = (prm.inner_ordering == HZ_ORD_MM) ? P.W2 : P.W2 - 1;
     const int64_t maxch = (P.mfw > P.mgw ? P.mfw : P.mgw) / 64;
     int64_t sp = prm.gram_splits ? prm.gram_splits : (512 + 2 * P.npairs - 1) / (2 * P.npairs);
     if (sp > 16) sp = 16;
@@ -169,7 +161,6 @@ static bool make_plan(const hz_params &prm, int64_t mf, int64_t mg, int64_t n, i
     P.o_gram = o; o = align256(o + es * (size_t)P.npairs * 2 * P.W2 * P.W2);
     P.o_zt = o; o = align256(o + es * (size_t)P.npairs * P.W2 * P.W2);
     P.o_otab = o; o = align256(o + sizeof(int) * (size_t)P.steps * P.npairs * 2);
-    P.o_itab = o; o = align256(o + sizeof(int16_t) * (size_t)P.isteps * P.w * 2);
     P.o_cnt = o; o = align256(o + sizeof(unsigned long long) * (size_t)P.steps * P.npairs * 4);
     P.o_status = o; o = align256(o + sizeof(int) * ST_NSLOTS);
     P.o_tot = o; o = align256(o + sizeof(unsigned long long) * SWEEP_TOT_N);
@@ -223,7 +214,6 @@ static Ptrs make_ptrs(const Plan &P, void *work)
     W.phase = nullptr;
     W.Zt = (double *)(b + P.o_zt);
     W.otab = (int *)(b + P.o_otab);
-    W.itab = (int16_t *)(b + P.o_itab);
     W.cnt = (unsigned long long *)(b + P.o_cnt);
     W.status = (int *)(b + P.o_status);
     W.tot = (unsigned long long *)(b + P.o_tot);
@@ -909,9 +899,7 @@ static int run_solve(const hz_params &prm, const Plan &P, void *work, size_t wor
         }
         const double tol = (prm.tol > 0.0) ? prm.tol : sqrt((double)P.n) * DBL_EPSILON;
         std::vector<int> otab;
-        std::vector<int16_t> itab;
         build_ordering<int>(prm.ordering, P.nblk, otab);
-        build_ordering<int16_t>(inner_table_kind(prm.inner_ordering), P.W2, itab);
         const int hs0[ST_NSLOTS] = {0, INT_MAX, 0, 0};
         int hs[ST_NSLOTS] = {0, INT_MAX, 0, 0};
         uint64_t tot_all = 0, tot_big = 0, tot_isw = 0, tot_skip = 0;
@@ -920,8 +908,6 @@ static int run_solve(const hz_params &prm, const Plan &P, void *work, size_t wor
         double offs[32];
         double last_off = 0.0;
         HZ_CHECK(hipMemcpyAsync(W.otab, otab.data(), otab.size() * sizeof(int),
-                                hipMemcpyHostToDevice, st));
-        HZ_CHECK(hipMemcpyAsync(W.itab, itab.data(), itab.size() * sizeof(int16_t),
                                 hipMemcpyHostToDevice, st));
         HZ_CHECK(hipMemcpyAsync(W.status, hs0, sizeof(hs0), hipMemcpyHostToDevice, st));
         DFArgs dfa;
@@ -955,8 +941,7 @@ static int run_solve(const hz_params &prm, const Plan &P, void *work, size_t wor
             dfa.tile_rows = P.df_tile_rows;
             dfa.part = (double *)(b + P.o_dpart);
             dfa.Zt = (double *)(b + P.o_dzt);
-            dfa.itab = W.itab;
-            dfa.isteps = P.isteps;
+            dfa.inner_ordering = prm.inner_ordering;
             dfa.inner_max = prm.inner_max_sweeps;
             dfa.sort = prm.sort;
             dfa.variant = prm.variant;
@@ -1269,10 +1254,10 @@ namespace hz {
 // counters) is staged on the host and copied in once; the per-pair working
 // arrays follow, each 256-byte aligned.
 struct BLayout {
-    int w = 0, W2 = 0, isteps = 0, inner_lp = 0, kmax = 0;
+    int w = 0, W2 = 0, inner_lp = 0, kmax = 0;
     int persistent = 0;                  // one launch for all sweeps (kb_persist)
     int64_t max_nw = 0, nptask = 0;
-    size_t o_probs = 0, o_tasks = 0, o_itab = 0, o_active = 0, o_pinfo = 0, o_pstatus = 0,
+    size_t o_probs = 0, o_tasks = 0, o_active = 0, o_pinfo = 0, o_pstatus = 0,
            o_nactive = 0, o_pcnt = 0, o_ptot = 0, meta = 0, total = 0;
     size_t o_ptask = 0, o_qhead = 0, o_pdone = 0, o_pfin = 0, o_psw = 0;
     std::vector<Plan> plan;              // per pair (n >= 2)
@@ -1305,7 +1290,6 @@ static bool plan_batched(const hz_params &prm, int batch, const int64_t *mf, con
     L.w = prm.w ? prm.w : (nmax <= 32 ? 8 : 16);
     q.w = L.w;
     L.W2 = 2 * L.w;
-    L.isteps = (prm.inner_ordering == HZ_ORD_MM) ? L.W2 : L.W2 - 1;
     L.inner_lp = inner_lanes_for(prm, L.W2);
     // The persistent schedule (default where it applies) runs a task's
     // inner solve with the whole workgroup of at least four waves: 2w = 64
@@ -1344,7 +1328,6 @@ static bool plan_batched(const hz_params &prm, int batch, const int64_t *mf, con
     size_t o = 0;
     L.o_probs = o; o = align256(o + sizeof(BProb) * (size_t)batch);
     L.o_tasks = o; o = align256(o + sizeof(int2) * (size_t)(tot > 0 ? tot : 1));
-    L.o_itab = o; o = align256(o + sizeof(int16_t) * (size_t)L.isteps * L.w * 2);
     L.otab_off.clear();
     for (int b : L.otab_nblk) {
         L.otab_off.push_back(o);
@@ -1440,14 +1423,12 @@ static int run_batched(const hz_params &prm, int batch, const int64_t *mf, const
         B.w = L.w;
         B.W2 = L.W2;
         B.inner_lp = L.inner_lp;
-        B.isteps = L.isteps;
         B.kmax = L.kmax;
         B.max_nw = L.max_nw;
         B.probs = (BProb *)(base + L.o_probs);
         B.tasks = (int2 *)(base + L.o_tasks);
         B.ntasks = L.ntasks;
         B.task_off = L.task_off;
-        B.itab = (int16_t *)(base + L.o_itab);
         B.active = (int *)(base + L.o_active);
         B.pinfo = (int *)(base + L.o_pinfo);
         B.pstatus = (int *)(base + L.o_pstatus);
@@ -1468,15 +1449,10 @@ static int run_batched(const hz_params &prm, int batch, const int64_t *mf, const
         int2 *ht = (int2 *)(hm + L.o_tasks);
         int *hact = (int *)(hm + L.o_active);
         int *hst = (int *)(hm + L.o_pstatus);
-        {
-            std::vector<int16_t> it;
-            build_ordering<int16_t>(inner_table_kind(prm.inner_ordering), L.W2, it);
-            memcpy(hm + L.o_itab, it.data(), it.size() * sizeof(int16_t));
-            for (size_t t = 0; t < L.otab_nblk.size(); ++t) {
-                std::vector<int> ot;
-                build_ordering<int>(prm.ordering, L.otab_nblk[t], ot);
-                memcpy(hm + L.otab_off[t], ot.data(), ot.size() * sizeof(int));
-            }
+        for (size_t t = 0; t < L.otab_nblk.size(); ++t) {
+            std::vector<int> ot;
+            build_ordering<int>(prm.ordering, L.otab_nblk[t], ot);
+            memcpy(hm + L.otab_off[t], ot.data(), ot.size() * sizeof(int));
         }
         for (int i = 0; i < batch; ++i) {
             hst[(size_t)i * ST_NSLOTS + ST_FAILPAIR] = INT_MAX;

@@ -22,14 +22,13 @@ struct Plan {
     int nblk;                 // N = nw / w block columns
     int npairs;               // N / 2 block pairs per step
     int steps;                // outer steps per sweep
-    int isteps;               // inner steps per inner sweep
     int splits;               // row splits of the Gram kernel
     int upd_rows;             // rows per wave in the update kernel
     int inner_lp;             // lanes per column pair in the inner solver (8 or 16)
     int is_complex;
     size_t esz;               // bytes per matrix element (8 or 16)
     // workspace offsets (bytes)
-    size_t o_fw, o_gw, o_zw, o_part, o_gram, o_zt, o_otab, o_itab, o_cnt, o_status, o_tot;
+    size_t o_fw, o_gw, o_zw, o_part, o_gram, o_zt, o_otab, o_cnt, o_status, o_tot;
     size_t o_sf, o_sg, o_sig, o_rank, o_border;
     size_t o_fs, o_gs, o_zs, o_offd;   // mixed form only (FP32 copies, off-diagonal measure)
     size_t o_qr[2];                    // pivot_qr only: triangles of the QR tree, two levels
@@ -47,7 +46,6 @@ struct Ptrs {
     double *Fw, *Gw, *Zw, *part, *gram, *Zt;
     unsigned long long *phase;   // optional per-(step, pair) phase clocks, or null
     int *otab;
-    int16_t *itab;
     unsigned long long *cnt;
     int *status;
     double *sf, *sg, *sig;
@@ -76,12 +74,11 @@ struct BProb {
 
 // Host-side plan of a batched solve (device pointers into one workspace).
 struct BPlan {
-    int batch, w, W2, inner_lp, isteps, kmax;
+    int batch, w, W2, inner_lp, kmax;
     int64_t max_nw;
     BProb *probs;
     int2 *tasks;                        // per step: (pair, block pair), largest pairs first
     std::vector<int> ntasks, task_off;  // per step
-    int16_t *itab;
     int *active, *pinfo, *pstatus, *nactive;
     unsigned long long *pcnt, *ptot;
     // persistent schedule: task list (pair, round << 12 | block pair), queue
@@ -206,8 +203,7 @@ struct DFArgs {
     int64_t tile_rows;
     double *part;                // steps x npairs x 2 x splits x 64 x 64
     double *Zt;                  // steps x npairs x 64 x 64
-    const int16_t *itab;
-    int isteps, inner_max, sort, variant;
+    int inner_ordering, inner_max, sort, variant;
     double tol;
     unsigned long long *cnt;     // steps x npairs x 4 (as the per-step kernels)
     int *status;

@@ -112,16 +112,17 @@ __global__ __launch_bounds__(256) void k_gram_sum(double *__restrict__ part, int
 //  2. Cholesky A_hat = F_hat^T F_hat, B_hat = G_hat^T G_hat (F_hat, G_hat
 //     upper triangular), one wave per matrix: for 2w = 64 (and 2w = 32 with
 //     two or more waves) in panels of 16 columns factored in registers
-//     (lane = row, entries by readlane) with the trailing lower tiles
-//     updated by FP64 MFMA; otherwise column by column, lane i keeping row
+//     (lane = row, entries by readlane, or by row broadcasts with the ring)
+//     with the trailing lower tiles updated by FP64 MFMA; otherwise column by column, lane i keeping row
 //     i, the new column of L broadcast through LDS (both matrices in one
 //     wave); a non-positive pivot flags HZ_ECHOL.
 //  3. Z_hat = diag(1/||g_hat_j||), F_hat, G_hat scaled by it.
 //  4. Inner sweeps (<= inner_max, stop after a sweep without big
-//     transformations, the rule of the outer sweeps), the columns in registers: per step, the LP lanes of
-//     a column pair form a_ii, a_jj, a_ij, b_ij, then the skip test, the 2x2
-//     transformation, criterion C1 and the sorting swap, and the columns pass
-//     on to the next step's pairs by lane exchanges or through LDS.
+//     transformations, the rule of the outer sweeps), the columns in
+//     registers: per step, the LP lanes of a column pair form a_ii, a_jj,
+//     a_ij, b_ij, then the skip test, the 2x2 transformation, criterion C1 and
+//     the sorting swap, and the columns pass on to the next step's pairs by
+//     lane exchanges or through LDS.
 //  5. Z_tilde = Z_hat Theta, Theta_jj = (||f_hat_j||^2+||g_hat_j||^2)^-1/2.
 // Counters per (step, pair): transformations, big ones, inner sweeps run.
 // ------------------------------------------------------------------------
