@@ -219,6 +219,12 @@ __device__ __forceinline__ double div_nr(double a, double b)
     return fma(r, fma(-b, q, a), q);
 }
 
+// x is positive, finite and no denormal (one instruction).
+__device__ __forceinline__ bool positive_normal(double x)
+{
+    return !__builtin_amdgcn_class(x, 0x3FF ^ (1 << 8));
+}
+
 // Scheduling fence between LDS traffic of lanes of one wave (LDS executes a
 // wave's operations in order; this only stops the compiler from moving
 // accesses across it).
@@ -257,7 +263,9 @@ __device__ __forceinline__ void wave_fence()
 // (criterion C1).  A' proportional to B' (h = D = 0) takes r = -sign(x), the
 // printed congruence with the sign of x carried onto the off-diagonal
 // entries so that it is one for x < 0 too; with keep (the pair is left alone;
-// the caller passes a_ij = x = 0) it takes r = 0, the identity.  An inner step is bound by the
+// the caller passes x = 0) it takes r = 0, the identity, whatever A' is.  Where a square of h or D overflows, or both underflow,
+// the root is a NaN and stays one, which the solve reports: a pivot like that
+// must not pass for one proportional to B'.  An inner step is bound by the
 // instructions of one wave (about five cycles each), and the transformation
 // with the sort keys was the largest part of them: about 43 instructions
 // instead of 110 took whole solves at the default parameters from 31.8 to
@@ -277,7 +285,8 @@ __device__ __forceinline__ void hz_real_2x2_fast(double aii, double ajj, double 
     const double y0 = __builtin_amdgcn_rcp(den);
     const double e = fma(-den, y0, 1.0);
     const double r0 = (num + num) * fma(y0, fma(e, e, e), y0);
-    const double r = (hyp2 > 0.0) ? r0 : (keep ? 0.0 : -copysign(1.0, x));
+    const bool prop = fabs(h) + fabs(D) == 0.0;
+    const double r = (keep || prop) ? (keep ? 0.0 : -copysign(1.0, x)) : r0;
     const double w = r + x, o = fma(r, x, 1.0);
     const double rt = rsqrt_nr(t2);
     rs = rsqrt_nr(fma(w, w, t2));
@@ -302,8 +311,9 @@ __device__ __forceinline__ void hz_real_2x2_fast(double aii, double ajj, double 
 // Eliminating the printed angles gives the same entries (their cosines divided
 // by t are rb, rs); with u + i v = e^(-i zeta) a the printed radicand t^2 (h^2 +
 // 4 v^2) + (2u - (a_bb + a_ss) x)^2 is the one above.  A' proportional to B'
-// takes r = -e^(i zeta) (-1 for beta = 0), the printed congruence; with keep (a =
-// beta = 0 passed) r = 0, the identity.
+// takes r = -e^(i zeta) (-1 for beta = 0), the printed congruence; with keep (beta =
+// 0 passed) r = 0, the identity, and NaNs stay, both as in the real form.
+// A radicand that rounding takes below zero counts as A' proportional to B'.
 __device__ __forceinline__ void hz_cplx_2x2_fast(double abb, double ass, double ar, double ai,
                                                  double br, double bi, bool keep, double &rb,
                                                  double &cbr, double &cbi, double &rs, double &csr,
@@ -315,20 +325,22 @@ __device__ __forceinline__ void hz_cplx_2x2_fast(double abb, double ass, double 
     const double m = fma(ai, br, -ar * bi), m2 = m + m;
     const double hyp2 = fma(-m2, m2, fma(t2 * h, h, fma(Dr, Dr, Di * Di)));
     const double nr = fma(ass, br, -ar), ni = fma(ass, bi, -ai);
-    const double p = h + sqrt_nr(hyp2);
-    const double q = fma(p, p, m2 * m2);                     // |denominator|^2
+    // half the denominator, p + i m: its square overflows no earlier than hyp2
+    const double p = 0.5 * (h + sqrt_nr(hyp2));
+    const double q = fma(p, p, m * m);
     const double y0 = __builtin_amdgcn_rcp(q);
     const double e = fma(-q, y0, 1.0);
     const double y = fma(y0, fma(e, e, e), y0);
-    const double k2 = y + y;
-    const bool reg = hyp2 > 0.0;
-    double rr = k2 * fma(nr, p, ni * m2), ri = k2 * fma(ni, p, -nr * m2);
-    if (!reg) {
-        // A' proportional to B', a pair left alone, or a radicand lost to rounding
+    double rr = y * fma(nr, p, ni * m), ri = y * fma(ni, p, -nr * m);
+    if (!positive_normal(hyp2)) {
         const double ix = (x2 > 0.0) ? rsqrt_nr(x2) : 0.0;
-        rr = keep ? 0.0 : (x2 > 0.0 ? -br * ix : -1.0);
-        ri = keep ? 0.0 : -bi * ix;
+        const bool prop = (hyp2 < 0.0) | (fabs(h) + fabs(Dr) + fabs(Di) == 0.0);
+        const bool zero = fabs(nr) + fabs(ni) == 0.0;       // also where 1 / q overflows
+        rr = prop ? (x2 > 0.0 ? -br * ix : -1.0) : (zero ? 0.0 : rr);
+        ri = prop ? -bi * ix : (zero ? 0.0 : ri);
     }
+    rr = keep ? 0.0 : rr;
+    ri = keep ? 0.0 : ri;
     const double wr = rr + br, wi = ri + bi;
     const double orr = fma(rr, br, fma(ri, bi, 1.0)), oi = fma(rr, bi, -ri * br);
     const double rt = rsqrt_nr(t2);

@@ -198,7 +198,7 @@ struct RealCols {
     // the larger transformed diagonal entry, which is b'' (or the larger
     // column of a pair that is orthogonal already).  first: x has the smaller
     // index (always, unless KEEP).  A pair that is left alone takes the
-    // identity -- its x and a count as zero, which gives it exactly -- so that
+    // identity -- its x counts as zero, which gives it exactly -- so that
     // the wave has one path; a wave in which every pair is left alone skips
     // it.  The lane masks are taken from plain comparisons, which cost one
     // instruction each.  Returns whether any pair of the wave changes.
@@ -219,7 +219,7 @@ struct RealCols {
         if ((m_rot | m_swap) == 0) return false;
         const bool orth = orth_a && orth_b;
         double rb, qb, rs, rr, t;
-        hz_real_2x2_fast(axx, ayy, orth ? 0.0 : axy, orth ? 0.0 : bxy, orth, rb, qb, rs, rr, t);
+        hz_real_2x2_fast(axx, ayy, axy, orth ? 0.0 : bxy, orth, rb, qb, rs, rr, t);
         count_big<GEN>(rb, rs, t, m_rot, A);
         // coefficients of x and y in b'' and s''
         const double bx = xs ? -qb : rb, by = xs ? rb : -qb;
@@ -283,8 +283,8 @@ struct CplxCols {
         // oriented from b to s
         const double sg = xs ? -1.0 : 1.0;
         double rb, cbr, cbi, rs, csr, csi, t;
-        hz_cplx_2x2_fast(xs ? ayy : axx, xs ? axx : ayy, orth ? 0.0 : ar, orth ? 0.0 : sg * ai,
-                         orth ? 0.0 : br, orth ? 0.0 : sg * bi, orth, rb, cbr, cbi, rs, csr, csi, t);
+        hz_cplx_2x2_fast(xs ? ayy : axx, xs ? axx : ayy, ar, sg * ai, orth ? 0.0 : br,
+                         orth ? 0.0 : sg * bi, orth, rb, cbr, cbi, rs, csr, csi, t);
         count_big<GEN>(rb, rs, t, m_rot, A);
         const double ox = xs ? rs : rb, oy = xs ? rb : rs;
         const double cxr = xs ? csr : cbr, cxi = xs ? csi : cbi;
