@@ -462,7 +462,16 @@ __device__ __forceinline__ void pointwise_solve(double *__restrict__ sF, double 
     unsigned chg_any = 0;
     int nsw = 0;
     auto step = [&](bool first) {
-        if (E::template step<GW, ND, KEEP, GEN>(C, first, A)) chg_any = 1;
+        if (E::template step<GW, ND, KEEP, GEN>(C, first, A)) {
+            chg_any = 1;
+            if (RING) {
+                // The ring's lane exchanges may come next, and what assembly
+                // writes the compiler does not wait for: two wait states
+                // from the last write, wherever it puts that.
+                __builtin_amdgcn_sched_barrier(0);
+                __asm__ volatile("s_nop 1");
+            }
+        }
     };
 
     if constexpr (RING) {
