@@ -384,12 +384,11 @@ __device__ __forceinline__ double mul_rd(double a, double b)
 #pragma clang fp contract(off)
     const double p = a * b;
     const double e = fma(a, b, -p);
-    if (!(e < 0.0)) return p;
-    long long bits = __double_as_longlong(p);
-    if (p > 0.0) bits -= 1;
-    else if (p < 0.0) bits += 1;
-    else bits = (long long)0x8000000000000001ull;   // below +-0: -denorm_min
-    return __longlong_as_double(bits);
+    // by selects: as branches, 64 of them to a step, they were most of it.  Away
+    // from zero for p <= 0 (below +-0: -denorm_min), towards it for p > 0.
+    const long long bits = __double_as_longlong((p == 0.0) ? -0.0 : p);
+    const long long below = bits + ((p > 0.0) ? -1 : 1);
+    return (e < 0.0) ? __longlong_as_double(below) : p;
 }
 
 // |re + i im|^2 by the simpler complex procedure of Appendix A: the
