@@ -404,7 +404,7 @@ int hz_dgsvd_batched_tune(const hz_params *p, int batch, const int64_t *m_f, con
 /* Short English description of a status code. */
 const char *hz_strerror(int status);
 
-/* Library version string. */
+/* Library version string; the autotuners take cached choices of this version only. */
 const char *hz_version(void);
 
 #ifdef __cplusplus

@@ -531,7 +531,9 @@ const char *hz_strerror(int status)
     }
 }
 
-const char *hz_version(void) { return "hzgsvd 0.2 (gfx950)"; }
+// Part of the tuner's keys: to be raised with any change of the kernels or of
+// their defaults, so that no choice timed on others is taken from a cache file.
+const char *hz_version(void) { return "hzgsvd 0.3 (gfx950)"; }
 
 int hz_eval_2x2(int64_t count, const double *in, double *out, void *stream)
 {
