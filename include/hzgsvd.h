@@ -113,10 +113,15 @@ typedef struct hz_params {
     int inner_ordering;   /* pointwise ordering inside a block pair: HZ_ORD_RR (default),
                              HZ_ORD_MM or HZ_ORD_RING (not with the dataflow schedule) */
     int w;                /* block-column width: 0 = default, else 8, 16 or 32 */
-    int inner_max_sweeps; /* inner sweeps per block step: 30 = FB (default), 1 = BO */
+    int inner_max_sweeps; /* inner sweeps per block step: 30 = FB (default), 1 = BO.  An
+                             inner solve ends before that after a sweep without big
+                             transformations (as `variant` counts them), the rule by
+                             which the outer sweeps end; it does not go on until no
+                             pair exceeds `tol` */
     int max_sweeps;       /* outer sweep cap (default 30, Algorithm 1) */
-    double tol;           /* relative-orthogonality threshold; <= 0 selects
-                             sqrt(n)*DBL_EPSILON (Section 2.1) */
+    double tol;           /* relative-orthogonality threshold, which decides whether a
+                             pair is transformed (not when the sweeps end); <= 0
+                             selects sqrt(n)*DBL_EPSILON (Section 2.1) */
     int sort;             /* 1 = per-step column sorting heuristic (default), 0 = none */
     double mixed_switch;  /* mixed form: switch to FP64 when the largest scaled
                              off-diagonal Gram entry of an FP32 sweep falls below

@@ -349,9 +349,12 @@ struct CplxCols {
 // The inner sweeps stop after one without big transformations, as the outer
 // ones do (Section 2.5): small ones leave the block diagonal to working
 // precision, and a further sweep only to see that there are none left cost an
-// eighth of the inner sweeps of full-block solves (2048 x 630 94.2 -> 87.8 ms,
-// the same errors against 64-bit references, also for sigma over twelve
-// orders of magnitude).
+// eighth of the inner sweeps of full-block solves (700 x 256 23.8 against 22.3
+// ms, 2048 x 630 91.4 against 85.2).  Over 680 pairs with sigma over six to
+// sixteen orders of magnitude, n = 16 ... 512, real and complex, in all
+// orderings and with QR pivot factors, the errors of sigma are 0.99 and the
+// largest departures of U^H U and V^H V from I 1.00 times those of the other
+// rule, and the same after a single sweep of a single block.
 template <class E, int W2, int LP, int ORD, bool GEN, bool LOWER>
 __device__ __forceinline__ void pointwise_solve(double *__restrict__ sF, double *__restrict__ sG,
                                                 double *__restrict__ sZ,
