@@ -164,18 +164,25 @@ struct InnerSide {
 };
 // Rows of Z per side workgroup of nw waves: four 16-row tiles per wave.
 inline int side_rows(int nw) { return 64 * nw; }
-// Whether Z goes aside.  The workgroups cost the launch 1.3 us, so Z has to be
-// large (n = 2048, 2w = 64: 8192 rows 76.9 -> 70.4 ms for 5 sweeps, 3072 rows
-// 45.5 -> 42.3; 6144x1536 41.3 -> 40.4; 4096x1024 60.0 -> 60.2 ms for 19) or a
-// large part of the rows (1100x1024 16.4 -> 15.7 ms for 5 sweeps), or other
-// work is there for them (mixed form: 198 -> 189 ms for 8192x2048); 2w = 32
-// gains nothing (1024x1024: 53.2 -> 53.5 ms for 20).  Beyond four workgroups
-// per idle compute unit (of 256) they would outlast the inner solve.
+// Whether Z goes aside (2w = 64; five sweeps, not aside -> aside).  The workgroups
+// cost the launch 1.3 us.  From n = 1536 on Z is large enough: 8192x2048 75.4 ->
+// 68.9 ms, 3072x2048 44.6 -> 41.7, 6144x1536 38.8 -> 38.0.  Between 1024 and 1536
+// it pays where the update's workgroups then make one round of the 256 compute
+// units instead of more than one: 1100x1024 15.2 -> 14.5, 1536x1024 15.2 -> 14.6,
+// but 1700x1024 15.3 -> 15.6, 2048x1024 15.5 -> 15.7, 1300x1280 20.1 -> 20.4.  Below
+// that it is lost: 4096x1024 58.6 -> 59.0 for 19 sweeps.  The mixed form has other
+// work for them too (8192x2048 195.6 -> 187.0).  Beyond four workgroups per idle
+// compute unit they would outlast the inner solve.
 inline bool z_aside(const Plan &P, const hz_params &prm)
 {
     if (P.W2 != 64 || prm.pivot_qr || P.npairs >= 256) return false;
     const int rows = side_rows(P.w * P.inner_lp / 64);
-    return (P.mixed || P.nzw >= 1536 || (P.nzw >= 1024 && 4 * P.nzw >= P.mfw + P.mgw)) &&
+    auto update_wgs = [&](int64_t m) {
+        const int64_t rpt = 4 * (int64_t)P.upd_rows;
+        return P.npairs * ((m + rpt - 1) / rpt);
+    };
+    const bool round = update_wgs(P.mfw + P.mgw) <= 256 && update_wgs(P.mfw + P.mgw + P.nzw) > 256;
+    return (P.mixed || P.nzw >= 1536 || (P.nzw >= 1024 && round)) &&
            P.npairs * ((P.nzw + rows - 1) / rows) <= 4 * (256 - P.npairs);
 }
 // Z_tilde of a step: with Z aside, the odd steps' in the buffer of the pivot
