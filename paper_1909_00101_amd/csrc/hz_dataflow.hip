@@ -136,7 +136,6 @@ __global__ __launch_bounds__(DF_NT) void k_sweep_df(DFArgs A)
                     pa, pa + S * W2SQ, S, W2SQ, A.inner_max, A.tol, A.sort, A.variant,
                     A.Zt + kl * W2SQ, A.cnt + kl * 4, A.status, k * 65536 + l, nullptr, lds);
             };
-            // (the ring is taken as round robin here)
             if (A.inner_ordering == HZ_ORD_MM) solve(std::integral_constant<int, HZ_ORD_MM>());
             else solve(std::integral_constant<int, HZ_ORD_RR>());
             sig = inner_done + kl;

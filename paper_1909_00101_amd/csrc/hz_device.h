@@ -225,18 +225,6 @@ __device__ __forceinline__ double rsqrt_lo(double x)
 
 __device__ __forceinline__ double sqrt_nr(double x) { return x * rsqrt_nr(x); }
 
-// a / b for finite b != 0: hardware reciprocal estimate r0 refined by one
-// third-order step r = r0 (1 + e + e^2), e = 1 - b r0, then a * r with one
-// residual correction.
-__device__ __forceinline__ double div_nr(double a, double b)
-{
-    const double r0 = __builtin_amdgcn_rcp(b);
-    const double e = fma(-b, r0, 1.0);
-    const double r = fma(r0, fma(e, e, e), r0);
-    const double q = a * r;
-    return fma(r, fma(-b, q, a), q);
-}
-
 // x is positive, finite and no denormal (one instruction).
 __device__ __forceinline__ bool positive_normal(double x)
 {
@@ -284,11 +272,9 @@ __device__ __forceinline__ void wave_fence()
 // the caller passes x = 0) it takes r = 0, the identity, whatever A' is.  Where a square of h or D overflows, or both underflow,
 // the root is a NaN and stays one, which the solve reports: a pivot like that
 // must not pass for one proportional to B'.  An inner step is bound by the
-// instructions of one wave (about five cycles each), and the transformation
-// with the sort keys was the largest part of them: about 43 instructions
-// instead of 110 took whole solves at the default parameters from 31.8 to
-// 28.0 ms (700 x 256) and from 121.8 to 107.4 ms (2048 x 630), and the tuned
-// 4096 x 1024 solve from 73.2 to 69.1 ms.
+// instructions of one wave (about five cycles each), of which this takes some
+// 43; the printed form with the sort keys took 110, the largest part of a step,
+// and whole solves 6 (4096 x 1024) to 13 % (2048 x 630) more.
 __device__ __forceinline__ void hz_real_2x2_fast(double aii, double ajj, double aij, double x,
                                                  bool keep, double &rb, double &qb, double &rs,
                                                  double &rr, double &t)

@@ -24,7 +24,7 @@ struct Plan {
     int steps;                // outer steps per sweep
     int splits;               // row splits of the Gram kernel
     int upd_rows;             // rows per wave in the update kernel
-    int inner_lp;             // lanes per column pair in the inner solver (8 or 16)
+    int inner_lp;             // lanes per column pair in the inner solver (4, 8 or 16)
     int is_complex;
     size_t esz;               // bytes per matrix element (8 or 16)
     // workspace offsets (bytes)

@@ -278,7 +278,7 @@ __device__ __forceinline__ void inner_solve(
         // 170 cycles a column, and the latency of LDS around the tiles.  Against
         // the form below (readlane, pivots kept by selects, two waves, and its
         // transposition, which the prescale makes up for by reading across): 2w =
-        // 64 10.0 -> 8.3 us, 2w = 32 4.3 -> 3.5, 4096x1024 59.8 -> 58.4 ms.  The
+        // 64 10.0 -> 8.3 us, 2w = 32 4.3 -> 3.5, 4096x1024 60.0 -> 58.65 ms.  The
         // other orderings keep that one: behind this one the compiler made their
         // sweeps 1 % slower (2w = 64, many sweeps: 291 -> 295 us).
         constexpr int NBK = W2 / 16;

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void k_gram_sum(double *__restrict__ part, int
 // Section 2.1 pointwise method on the factors, Section 2.4 Theta rescale,
 // Section 2.5 counters; Sections 3.5.2-3.5.3 for the shared-memory flow).
 // One workgroup per block pair, NT = (W2/2) * LP threads: LP lanes per
-// column pair of an inner step, RPL = W2/LP rows per lane.  Steps:
+// column pair of an inner step, W2/LP rows per lane.  Steps:
 //  1. A_hat, B_hat = sum of the Gram partials (split order) into LDS.
 //  2. Cholesky A_hat = F_hat^T F_hat, B_hat = G_hat^T G_hat (F_hat, G_hat
 //     upper triangular), one wave per matrix: for 2w = 64 (and 2w = 32 with
@@ -471,8 +471,9 @@ void launch_prescale_real(const Plan &P, const Ptrs &W, const double *F, int64_t
 // Whether the inner solver adds the Gram's row-split partials itself: where
 // they are few bytes for its one workgroup, always for 2w <= 32 (2w = 32: 8
 // partials cost it 0.5 us and 16 2.4 us, k_gram_sum 2.4 us and the gap before
-// it), up to 4 for 2w = 64 (1.8 us; 8 cost 4.4 us and 4096x1024 60.6 -> 61.4
-// ms).  The off-diagonal measure of the FP32 phase takes the sums.
+// it: 4096x1024 shortened, w = 16, 55.4 with the kernel, 52.8 ms without), up to
+// 4 for 2w = 64 (1.8 us: 63.5 and 63.25 ms; 8 cost 4.4 us: 58.65 ms with the
+// kernel, 59.75 without).  The off-diagonal measure of the FP32 phase takes the sums.
 static bool inner_sums(const Plan &P, bool f32) { return !f32 && (P.W2 <= 32 || P.splits <= 4); }
 
 template <int W2, int LP>
