@@ -104,16 +104,15 @@ static int w_ok_for(const hz_params &p, int is_complex)
     return !is_complex || p.w == 0 || p.w == 8 || p.w == 16;
 }
 
-// Lanes per column pair in the inner solver.  One inner sweep of 16 pivot
-// pairs on which every pair rotates, 8 against 16 lanes: 2w = 32 22.4 against
-// 18.6 us in round robin and 17.0 against 14.2 in the ring ordering (a step is
-// bound by the instructions that do not shrink with the lanes' shares of the
-// columns, so more waves win); 2w = 64 72.1 against 68.5 in round robin, but 46.4
-// against 53.2 in the ring ordering, which moves columns between lanes and
-// whose second wave per SIMD would only repeat the 2x2 transformations.  2w = 16
-// has 8 column pairs: 8 lanes make one wave.  Complex 2w = 32 (twice the
-// products per lane): 28.8 against 20.3 us of inner sweeps in the ring ordering
-// of the 3072/2048 x 1024 pair.
+// Lanes per column pair in the inner solver.  One inner sweep of steps in which
+// every pair rotates, 8 against 16 lanes: 2w = 32 21.6 against 18.3 us in round
+// robin and 16.3 against 14.3 in the ring ordering (a step is bound by the
+// instructions that do not shrink with the lanes' shares of the columns, so more
+// waves win); 2w = 64 71.1 against 68.6 in round robin, but 47.0 against 52.3 in
+// the ring ordering, which moves columns between lanes and whose second wave per
+// SIMD would only repeat the 2x2 transformations.  2w = 16 has 8 column pairs: 8
+// lanes make one wave.  Complex 2w = 32 (twice the products per lane): 43.9
+// against 33.4 us in round robin and 35.7 against 26.2 in the ring ordering.
 static int inner_lanes_for(const hz_params &prm, int W2)
 {
     if (W2 == 16) return 8;

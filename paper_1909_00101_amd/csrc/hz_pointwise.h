@@ -334,17 +334,17 @@ struct CplxCols {
 // (from the lowest to the one above the highest) while the others pass only
 // their y on; the steps of further sweeps go on from where the last one
 // stopped.  That halves the LDS traffic for eight more selects and one
-// wave's extra stores and loads: 68.5 against 84.4 us for an inner sweep at 2w
+// wave's extra stores and loads: 68.6 against 84.4 us for an inner sweep at 2w
 // = 64 with 16 lanes, but 20.4 against 19.9 at 2w = 32.
 //
 // Bound: the instructions of one or two waves per SIMD, about five cycles
 // each from one wave, and in LDS the stores, 13 cycles of a compute unit for
 // 64 lanes x 16 bytes.  With every column handed on through LDS after every
 // step, the pivot sums taken one by one and the orderings read from a table,
-// one inner sweep of 16 pivot pairs on which every pair rotates took, before
-// and now: ring ordering 64.5 -> 46.4 us (2w = 64, 8 lanes) and 21.5 -> 14.2
-// (2w = 32, 16 lanes); round robin 86.9 -> 68.5 (2w = 64, 16 lanes) and 25.5 ->
-// 18.6 (2w = 32, 8 -> 16 lanes).
+// one inner sweep of the 4096 x 1024 pair's first steps, where every pair
+// rotates, took, before and now: ring ordering 73.6 -> 47.0 us (2w = 64, 8 lanes)
+// and 24.5 -> 14.3 (2w = 32, 16 lanes); round robin 96.8 -> 68.6 (2w = 64, 16
+// lanes) and 28.6 -> 18.3 (2w = 32, 8 -> 16 lanes).
 //
 // The inner sweeps stop after one without big transformations, as the outer
 // ones do (Section 2.5): small ones leave the block diagonal to working
